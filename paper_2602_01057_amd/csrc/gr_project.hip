@@ -3,16 +3,16 @@
 // backward pass.
 //
 // One wave64 owns one packet of 64 consecutive rays (one lane per ray):
-//  1. the rays' bounding "beam" is built once per packet: a frame (a, e1, e2)
-//     from the first ray's direction, and per-ray intercepts X and slopes S of
-//     every line x(z) = X + z S in that frame, reduced to [min, max] ranges
-//     with DPP;
+//  1. the packet's rays are taken in runs that one "beam" bounds well (an
+//     ordinary packet is one run, next_run in gr_trace.h): every line as
+//     x(z) = X + z S across the coordinate axis it mostly follows, and the
+//     run's [min, max] of x in three planes, reduced with DPP;
 //  2. the wave walks the 64-wide box hierarchy over the Morton-ordered leaves
 //     (64 child boxes tested against the beam per wave step, pending nodes on
 //     a per-wave LDS stack), or the binary LBVH with per-ray slab tests;
 //  3. at a leaf, up to 64 Gaussians are tested lane-parallel against the beam
-//     (support widths of each kappa ellipsoid along a, e1, e2), giving a
-//     64-bit candidate mask;
+//     (the mean's offset at its depth against the beam's and the kappa
+//     ellipsoid's shadow's half widths), giving a 64-bit candidate mask;
 //  4. for each candidate the 80-byte Gaussian record is fetched with scalar
 //     loads and every lane evaluates the closed form for its ray.
 //
@@ -55,8 +55,8 @@ namespace gr {
 // first evaluation (hold_records, as the recording loop of the fused pass
 // does) ran this kernel 4% slower: more scalar registers spill at 8 waves.
 template <bool kStats>
-__device__ inline void leaf_forward(const SceneView &S, const Ray &R, int64_t start, uint64_t mask,
-                                    float k2, bool active, double &acc, uint32_t &n_inc,
+__device__ inline void leaf_forward(const SceneView &S, const RayD &R, int64_t start, uint64_t mask,
+                                    float k2, double &acc, uint32_t &n_inc,
                                     uint32_t &n_hitc) {
     while (mask) {
         const int j0 = __builtin_ctzll(mask);
@@ -68,20 +68,20 @@ __device__ inline void leaf_forward(const SceneView &S, const Ray &R, int64_t st
         const GaussRec G1 = sload(S.rec, start + j1);
         PairCore c;
         float D, r;
-        pair_core(G0.mu, G0.P, R.o64, R.d64, R.dd, c);
+        pair_core(G0.mu, G0.P, R.o, R.d, R.dd, c);
         pair_D(c, D, r);
-        if (kStats) n_hitc += ballot(active && D <= k2) != 0 ? 1u : 0u;
+        if (kStats) n_hitc += ballot(D <= k2) != 0 ? 1u : 0u;
         if (D <= k2) {
             acc += double(G0.rho_c * r * gauss_exp(D));
-            if (kStats) n_inc += active ? 1u : 0u;
+            if (kStats) ++n_inc;
         }
         if (two) {
-            pair_core(G1.mu, G1.P, R.o64, R.d64, R.dd, c);
+            pair_core(G1.mu, G1.P, R.o, R.d, R.dd, c);
             pair_D(c, D, r);
-            if (kStats) n_hitc += ballot(active && D <= k2) != 0 ? 1u : 0u;
+            if (kStats) n_hitc += ballot(D <= k2) != 0 ? 1u : 0u;
             if (D <= k2) {
                 acc += double(G1.rho_c * r * gauss_exp(D));
-                if (kStats) n_inc += active ? 1u : 0u;
+                if (kStats) ++n_inc;
             }
         }
     }
@@ -121,7 +121,7 @@ __device__ inline void pair_core32(const GaussRec32 &G, const Ray &R, float inv_
 // leaf_forward in the FP32 precision mode (compact records, two per step).
 template <bool kStats>
 __device__ inline void leaf_forward32(const SceneView &S, const Ray &R, float inv_dd, int64_t start,
-                                      uint64_t mask, float k2, bool active, double &acc, uint32_t &n_inc,
+                                      uint64_t mask, float k2, double &acc, uint32_t &n_inc,
                                       uint32_t &n_hitc) {
     while (mask) {
         const int j0 = __builtin_ctzll(mask);
@@ -134,17 +134,17 @@ __device__ inline void leaf_forward32(const SceneView &S, const Ray &R, float in
         const GaussRec32 G1 = sload(rec32, start + j1);
         float D, r;
         pair_core32(G0, R, inv_dd, D, r);
-        if (kStats) n_hitc += ballot(active && D <= k2) != 0 ? 1u : 0u;
+        if (kStats) n_hitc += ballot(D <= k2) != 0 ? 1u : 0u;
         if (D <= k2) {
             acc += double(G0.rho_c * r * gauss_exp(D));
-            if (kStats) n_inc += active ? 1u : 0u;
+            if (kStats) ++n_inc;
         }
         if (two) {
             pair_core32(G1, R, inv_dd, D, r);
-            if (kStats) n_hitc += ballot(active && D <= k2) != 0 ? 1u : 0u;
+            if (kStats) n_hitc += ballot(D <= k2) != 0 ? 1u : 0u;
             if (D <= k2) {
                 acc += double(G1.rho_c * r * gauss_exp(D));
-                if (kStats) n_inc += active ? 1u : 0u;
+                if (kStats) ++n_inc;
             }
         }
     }
@@ -163,23 +163,22 @@ __device__ inline void packet_forward(const LaunchTable &T, int64_t packet, int 
     float *out = sg.out;
     Ray R;
     load_ray(sg.ro, sg.rd, sg.stride, P.ray, R);
-    Beam B;
-    build_beam(R, B);
     double acc = 0.0;
-    const float k2 = S.kappa2;
     uint32_t n_inc = 0, n_cand = 0, n_leaf = 0, n_hitc = 0;
     const float inv_dd = kCompact ? 1.0f / (R.d[0] * R.d[0] + R.d[1] * R.d[1] + R.d[2] * R.d[2]) : 0.0f;
-    traverse_any(T.traversal, S, R, B, P.active, lane, stack, [&](int l) {
+    traverse_runs(T.traversal, S, R, ballot(P.active), lane, stack, [&](int l, bool in, const RayD &Q, const Beam &B) {
         int64_t start;
         const uint64_t mask = leaf_candidates(S, B, l, lane, start);
+        // lanes outside the run compare against a cutoff that no D >= 0 passes
+        const float k2 = in ? S.kappa2 : -1.0f;
         if (kStats) {
             ++n_leaf;
             n_cand += __builtin_popcountll(mask);
         }
         if constexpr (kCompact)
-            leaf_forward32<kStats>(S, R, inv_dd, start, mask, k2, P.active, acc, n_inc, n_hitc);
+            leaf_forward32<kStats>(S, R, inv_dd, start, mask, k2, acc, n_inc, n_hitc);
         else
-            leaf_forward<kStats>(S, R, start, mask, k2, P.active, acc, n_inc, n_hitc);
+            leaf_forward<kStats>(S, Q, start, mask, k2, acc, n_inc, n_hitc);
     });
     if (P.active) out[P.out] = float(acc);
     if (kStats) {
@@ -446,11 +445,8 @@ struct HitList {
 
 // Forward sum over one leaf's candidates (as leaf_forward), also recording the
 // packet's hit list.
-__device__ inline void leaf_forward_hits(const SceneView &S, const Ray &R, int64_t start, uint64_t mask,
-                                         float k2, bool active, double &acc, HitList &H, int lane) {
-    // A lane past the last ray compares against a negative cutoff, which no
-    // D >= 0 passes: the ballot is then one compare.
-    const float k2a = active ? k2 : -1.0f;
+__device__ inline void leaf_forward_hits(const SceneView &S, const RayD &R, int64_t start, uint64_t mask,
+                                         float k2a, double &acc, HitList &H, int lane) {
     while (mask) {
         const int j0 = __builtin_ctzll(mask);
         mask &= mask - 1;
@@ -462,7 +458,7 @@ __device__ inline void leaf_forward_hits(const SceneView &S, const Ray &R, int64
         hold_records(G0, G1);
         PairCore c;
         float D, r;
-        pair_core(G0.mu, G0.P, R.o64, R.d64, R.dd, c);
+        pair_core(G0.mu, G0.P, R.o, R.d, R.dd, c);
         pair_D(c, D, r);
         const uint64_t h0 = __builtin_amdgcn_ballot_w64(D <= k2a);
         if (h0) {
@@ -473,7 +469,7 @@ __device__ inline void leaf_forward_hits(const SceneView &S, const Ray &R, int64
             H.record(lane, start + j0, h0);
         }
         if (two) {
-            pair_core(G1.mu, G1.P, R.o64, R.d64, R.dd, c);
+            pair_core(G1.mu, G1.P, R.o, R.d, R.dd, c);
             pair_D(c, D, r);
             const uint64_t h1 = __builtin_amdgcn_ballot_w64(D <= k2a);
             if (h1) {
@@ -602,17 +598,26 @@ __device__ inline float loss_weight(int kind, float I, float y, float b, double 
     return float(1.0 - double(y) / Ib);
 }
 
-// Gaussian-major backward of one packet by re-traversal: the candidates of the
-// traversal go into the per-wave LDS list; every 64 of them are one batch.
+// Gaussian-major backward of one packet by re-traversal: the candidates of
+// the traversal go into the per-wave LDS list; every 64 of them are one batch.
+// A Gaussian can be a candidate of several of the packet's runs, so a batch
+// ends with its run and takes that run's rays only.
 template <class Rays>
-__device__ inline void retraverse_backward(const LaunchTable &T, const SceneView &S, const Ray &R,
-                                           const Beam &B, TravLds &Lt, const Rays &rays, uint64_t live_mask,
-                                           bool live, int lane, float k2, float *acc) {
-    int count = 0;  // wave-uniform number of listed candidates
-    traverse_any(T.traversal, S, R, B, live, lane, Lt.stack, [&](int l) {
+__device__ inline void retraverse_backward(const LaunchTable &T, const SceneView &S, const Ray &R, TravLds &Lt,
+                                           const Rays &rays, uint64_t live_mask, int lane, float k2, float *acc) {
+    int count = 0;        // wave-uniform number of listed candidates
+    uint64_t listed = 0;  // the rays they are for
+    traverse_runs(T.traversal, S, R, live_mask, lane, Lt.stack, [&](int l, bool in, const RayD &Q, const Beam &B) {
         int64_t start;
         const uint64_t mask = leaf_candidates(S, B, l, lane, start);
         if (!mask) return;
+        const uint64_t run = ballot(in);
+        if (run != listed) {
+            if (count > 0) backward_batch(S, Lt, rays, count, listed, lane, k2, acc);
+            __builtin_amdgcn_wave_barrier();
+            count = 0;
+            listed = run;
+        }
         if ((mask >> lane) & 1ull) {
             const int pos = count + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
             Lt.cand[pos] = int32_t(start + lane);
@@ -620,7 +625,7 @@ __device__ inline void retraverse_backward(const LaunchTable &T, const SceneView
         count += __builtin_popcountll(mask);
         __builtin_amdgcn_wave_barrier();
         if (count >= 64) {
-            backward_batch(S, Lt, rays, 64, live_mask, lane, k2, acc);
+            backward_batch(S, Lt, rays, 64, listed, lane, k2, acc);
             const int rest = count - 64;
             int moved = 0;
             if (lane < rest) moved = Lt.cand[64 + lane];
@@ -630,7 +635,7 @@ __device__ inline void retraverse_backward(const LaunchTable &T, const SceneView
             count = rest;
         }
     });
-    if (count > 0) backward_batch(S, Lt, rays, count, live_mask, lane, k2, acc);
+    if (count > 0) backward_batch(S, Lt, rays, count, listed, lane, k2, acc);
 }
 
 template <bool kFused>
@@ -645,8 +650,6 @@ __device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int
     const SceneView &S = T.scenes[sg.scene];
     Ray R;
     load_ray(sg.ro, sg.rd, sg.stride, P.ray, R);
-    Beam B;
-    build_beam(R, B);
     const float k2 = S.kappa2;
     if constexpr (kFused) {
         float *acc = sg.acc;
@@ -655,20 +658,20 @@ __device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int
         double sum = 0.0;
         if (T.hit_cap > 0 && hit_g) {
             HitList H{hit_g, hit_m, T.hit_cap, 0, 0, false, 0u, 0u, 0u};
-            traverse_any(T.traversal, S, R, B, P.active, lane, L->t.stack, [&](int l) {
+            traverse_runs(T.traversal, S, R, ballot(P.active), lane, L->t.stack, [&](int l, bool in, const RayD &Q, const Beam &B) {
                 int64_t start;
                 const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-                leaf_forward_hits(S, R, start, mask, k2, P.active, sum, H, lane);
+                leaf_forward_hits(S, Q, start, mask, in ? k2 : -1.0f, sum, H, lane);
             });
             H.flush(lane);
             listed = !H.overflow;
             n_ent = H.n;
         } else {
             uint32_t dummy = 0, dummy2 = 0;
-            traverse_any(T.traversal, S, R, B, P.active, lane, L->t.stack, [&](int l) {
+            traverse_runs(T.traversal, S, R, ballot(P.active), lane, L->t.stack, [&](int l, bool in, const RayD &Q, const Beam &B) {
                 int64_t start;
                 const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-                leaf_forward<false>(S, R, start, mask, k2, P.active, sum, dummy, dummy2);
+                leaf_forward<false>(S, Q, start, mask, in ? k2 : -1.0f, sum, dummy, dummy2);
             });
         }
         const float I = float(sum);
@@ -700,7 +703,7 @@ __device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int
             drain_hits(S, L, mine, hit_g, hit_m, n_ent, live_mask, lane, k2, acc);
             return;
         }
-        retraverse_backward(T, S, R, B, L->t, RaysInLanes{mine}, live_mask, live, lane, k2, acc);
+        retraverse_backward(T, S, R, L->t, RaysInLanes{mine}, live_mask, lane, k2, acc);
     } else {
         float *acc = A.acc;
         const float w = P.active ? A.grad_out[P.out] : 0.0f;
@@ -711,13 +714,13 @@ __device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int
         if (live) {
             RayRec &rr = L->rays[lane];
             for (int k = 0; k < 3; ++k) {
-                rr.o[k] = R.o64[k];
-                rr.d[k] = R.d64[k];
+                rr.o[k] = R.o[k];
+                rr.d[k] = R.d[k];
             }
             rr.w = w;
         }
         __builtin_amdgcn_wave_barrier();
-        retraverse_backward(T, S, R, B, L->t, RaysInLds{L->rays}, live_mask, live, lane, k2, acc);
+        retraverse_backward(T, S, R, L->t, RaysInLds{L->rays}, live_mask, lane, k2, acc);
     }
 }
 

@@ -346,14 +346,25 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
     if (!locate_packet(T, packet, lane, P)) return;
     const Segment &sg = T.segs[P.seg];
     const SceneView &S = T.scenes[sg.scene];
-    Ray R;
-    load_ray(sg.ro, sg.rd, sg.stride, P.ray, R);
-    Beam B;
-    build_beam(R, B);
-    const float k2 = S.kappa2;
     const TofBins tb = tof_bins(A);
     const bool tof = tb.nb > 0;
     const double c0 = double(ray_center(A, P.ray)) - tb.half;
+    // run by run, each with sums of its own that are written before the next
+    // (so that they take no registers while a run's beam is built)
+    uint64_t todo = ballot(P.active);
+    const uint64_t all = todo;
+    uint64_t lines = 0;  // written
+    const Extent E = scene_extent(S);
+    while (todo) {
+    Ray R;
+    load_ray(sg.ro, sg.rd, sg.stride, P.ray, R);
+    Beam B;
+    const uint64_t run = S.n > 0 ? next_run(E, R, todo, lane, B) : (todo = 0);
+    if (!run) continue;
+    lines |= run;
+    const bool in = (run >> lane) & 1ull;
+    const RayD V = widen_ray(R);
+    const float k2 = in ? S.kappa2 : -1.0f;
     double acc[kBins];
 #pragma unroll
     for (int b = 0; b < kBins; ++b) acc[b] = 0.0;
@@ -371,7 +382,7 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
     auto pair_in = [&](const GaussRec &G) __attribute__((always_inline)) {
         PairCore c;
         float D, r;
-        pair_core(G.mu, G.P, R.o64, R.d64, R.dd, c);
+        pair_core(G.mu, G.P, V.o, V.d, V.dd, c);
         pair_D(c, D, r);
         if (D <= k2) {
             const float Tv = G.rho_c * r * gauss_exp(D);
@@ -389,7 +400,7 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
             }
         }
     };
-    traverse_any(T.traversal, S, R, B, P.active, lane, stack, [&](int l) {
+    traverse_run(T.traversal, S, R, B, in, lane, stack, [&](int l) {
         int64_t start;
         uint64_t mask = leaf_candidates(S, B, l, lane, start);
         // two candidates per step (their records load together)
@@ -416,17 +427,27 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
         }
     });
     while (ballot(cnt > 0)) bin_step();
-    if (P.active) {
-        const float a = ray_atten(A, P.ray);
-        const int nout = tof ? tb.nb : 1;
-#pragma unroll
-        for (int b = 0; b < kBins; ++b)
-            if (b < nout) A.out[int64_t(b) * A.n_rays + P.out] = float(double(a) * acc[b]);
+    if (in) {
+        const float att = ray_atten(A, P.ray);
+        // (opaque values: otherwise the bins' offsets and masks are all held
+        // through the traversal)
+        float *out = A.out + P.out;
+        int64_t stride = A.n_rays;
+        int n = tof ? tb.nb : 1;
+        asm volatile("" : "+v"(out), "+s"(stride), "+s"(n));
+        bins_until<0, kBins>(n, [&](auto b) {
+            if (b < n) *out = float(double(att) * acc[b]);
+            out += stride;
+        });
     }
+    }
+    // no line (zero or not finite), or no scene
+    if (((all & ~lines) >> lane) & 1ull)
+        for (int b = 0; b < (tof ? tb.nb : 1); ++b) A.out[int64_t(b) * A.n_rays + P.out] = 0.0f * ray_atten(A, P.ray);
 }
 
 template <int kBins>
-__global__ __launch_bounds__(256) void k_forward_tof(LaunchTable T, TofArgs A) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kBins > 16 ? 3 : 4))) void k_forward_tof(LaunchTable T, TofArgs A) {
     extern __shared__ __align__(16) unsigned char tof_lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
@@ -594,8 +615,6 @@ __device__ inline void packet_backward_tof(const LaunchTable &T, const TofArgs &
     const SceneView &S = T.scenes[sg.scene];
     Ray R;
     load_ray(sg.ro, sg.rd, sg.stride, P.ray, R);
-    Beam B;
-    build_beam(R, B);
     const float k2 = S.kappa2;
     const TofBins tb = tof_bins(A);
     const int nw = tb.nb > 0 ? tb.nb : 1;
@@ -620,9 +639,10 @@ __device__ inline void packet_backward_tof(const LaunchTable &T, const TofArgs &
     mine.c = ray_center(A, P.ray);
     float *acc = A.acc;
     TofPending pe{0, 0u, 0ull};
-    traverse_any(T.traversal, S, R, B, live, lane, L.stack, [&](int l) {
+    traverse_runs(T.traversal, S, R, ballot(live), lane, L.stack, [&](int l, bool in, const RayD &V, const Beam &B) {
         int64_t start;
         uint64_t mask = leaf_candidates(S, B, l, lane, start);
+        const float k2r = in ? k2 : -1.0f;
         while (mask) {
             const int j0 = __builtin_ctzll(mask);
             mask &= mask - 1;
@@ -634,14 +654,14 @@ __device__ inline void packet_backward_tof(const LaunchTable &T, const TofArgs &
             hold_records(G0, G1);
             PairCore c;
             float D, r;
-            pair_core(G0.mu, G0.P, R.o64, R.d64, R.dd, c);
+            pair_core(G0.mu, G0.P, V.o, V.d, V.dd, c);
             pair_D(c, D, r);
-            const uint64_t h0 = ballot(live && D <= k2);
+            const uint64_t h0 = ballot(D <= k2r);
             if (h0) pe.put(lane, start + j0, h0);
             if (two) {
-                pair_core(G1.mu, G1.P, R.o64, R.d64, R.dd, c);
+                pair_core(G1.mu, G1.P, V.o, V.d, V.dd, c);
                 pair_D(c, D, r);
-                const uint64_t h1 = ballot(live && D <= k2);
+                const uint64_t h1 = ballot(D <= k2r);
                 if (h1) pe.put(lane, start + j1, h1);
             }
             if (pe.n > kTofWin - 2) {
