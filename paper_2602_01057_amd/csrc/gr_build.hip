@@ -292,14 +292,16 @@ __global__ __launch_bounds__(256) void k_gather(const float *__restrict__ mean,
                                                 const float *__restrict__ scale,
                                                 const float *__restrict__ quat,
                                                 const float *__restrict__ dens, int64_t n,
-                                                float kappa, const uint32_t *__restrict__ order,
+                                                float kappa, int32_t leaf, const uint32_t *__restrict__ order,
                                                 GaussRec *__restrict__ rec,
                                                 GaussRec32 *__restrict__ rec32,
+                                                char *__restrict__ axis, size_t axis_stride,
                                                 float *__restrict__ cull,
                                                 float *__restrict__ aabb) {
     const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (g >= n) return;
     const int64_t i = order[g];
+    float *leaf_cull = cull + (g / leaf) * leaf * kCullFields + g % leaf;
     double mu[3], s[3], q[4], rho;
     GaussRec r;
     if (i >= n || !load_params(mean, scale, quat, dens, n, i, mu, s, q, rho)) {
@@ -314,7 +316,10 @@ __global__ __launch_bounds__(256) void k_gather(const float *__restrict__ mean,
         c.rho_c = 0.0f;
         c.pad[0] = c.pad[1] = c.pad[2] = 0.0f;
         rec32[g] = c;
-        for (int f = 0; f < kCullFields; ++f) cull[f * n + g] = __builtin_nanf("");
+        AxisRec a = {};
+        a.m1 = a.m2 = a.mk = __builtin_nan("");
+        for (int k = 0; k < 3; ++k) reinterpret_cast<AxisRec *>(axis + k * axis_stride)[g] = a;
+        for (int f = 0; f < kCullFields; ++f) leaf_cull[f * leaf] = __builtin_nanf("");
         for (int k = 0; k < 3; ++k) {
             aabb[g * 6 + k] = FLT_MAX;
             aabb[g * 6 + 3 + k] = -FLT_MAX;
@@ -352,16 +357,35 @@ __global__ __launch_bounds__(256) void k_gather(const float *__restrict__ mean,
     c.rho_c = r.rho_c;
     c.pad[0] = c.pad[1] = c.pad[2] = 0.0f;
     rec32[g] = c;
+    // views along the axes; det P Sigma_kk is the determinant of P's (t1, t2)
+    // block, so l22 = sqrt(det / P11) loses nothing to cancellation
+    const double iv = 1.0 / (s[0] * s[1] * s[2]);
+    for (int k = 0; k < 3; ++k) {
+        const int t1 = (k + 1) % 3, t2 = (k + 2) % 3;
+        AxisRec a;
+        a.m1 = mu[t1];
+        a.m2 = mu[t2];
+        a.mk = mu[k];
+        a.h = 1.0 / Sg[k][k];
+        a.s1 = Sg[t1][k] * a.h;
+        a.s2 = Sg[t2][k] * a.h;
+        a.l11 = sqrt(Pm[t1][t1]);
+        a.l21 = Pm[t1][t2] / a.l11;
+        a.l22 = iv * sqrt(Sg[k][k]) / a.l11;
+        a.rho_c = r.rho_c;
+        a.pad = 0.0f;
+        reinterpret_cast<AxisRec *>(axis + k * axis_stride)[g] = a;
+    }
     const double k2 = double(kappa) * double(kappa);
-    cull[0 * n + g] = float(mu[0]);
-    cull[1 * n + g] = float(mu[1]);
-    cull[2 * n + g] = float(mu[2]);
-    cull[3 * n + g] = float(k2 * Sg[0][0]);
-    cull[4 * n + g] = float(k2 * Sg[1][1]);
-    cull[5 * n + g] = float(k2 * Sg[2][2]);
-    cull[6 * n + g] = float(k2 * Sg[0][1]);
-    cull[7 * n + g] = float(k2 * Sg[0][2]);
-    cull[8 * n + g] = float(k2 * Sg[1][2]);
+    leaf_cull[0 * leaf] = float(mu[0]);
+    leaf_cull[1 * leaf] = float(mu[1]);
+    leaf_cull[2 * leaf] = float(mu[2]);
+    leaf_cull[3 * leaf] = float(k2 * Sg[0][0]);
+    leaf_cull[4 * leaf] = float(k2 * Sg[1][1]);
+    leaf_cull[5 * leaf] = float(k2 * Sg[2][2]);
+    leaf_cull[6 * leaf] = float(k2 * Sg[0][1]);
+    leaf_cull[7 * leaf] = float(k2 * Sg[0][2]);
+    leaf_cull[8 * leaf] = float(k2 * Sg[1][2]);
     for (int k = 0; k < 3; ++k) {
         const float e = float(double(kappa) * sqrt(Sg[k][k])) * (1.0f + kBoxRel) + kBoxAbs;
         aabb[g * 6 + k] = float(mu[k]) - e;
@@ -560,9 +584,11 @@ hipError_t enqueue_refit(const gr_scene &sc, const Layout &L, hipStream_t st) {
     if (n > 0) {
         const uint32_t *order = reinterpret_cast<const uint32_t *>(base + L.vals0);
         k_bounds<<<blocks_for(n, 256), 256, 0, st>>>(sc.mean, sc.scale, sc.quat, sc.density, n, hdr);
-        k_gather<<<blocks_for(n, 256), 256, 0, st>>>(sc.mean, sc.scale, sc.quat, sc.density, n, sc.kappa, order,
+        k_gather<<<blocks_for(n, 256), 256, 0, st>>>(sc.mean, sc.scale, sc.quat, sc.density, n, sc.kappa, L.leaf, order,
                                                       reinterpret_cast<GaussRec *>(base + L.rec),
                                                       reinterpret_cast<GaussRec32 *>(base + L.rec32),
+                                                      base + L.axis,
+                                                      align256(size_t(n) * sizeof(AxisRec)),
                                                       reinterpret_cast<float *>(base + L.cull),
                                                       reinterpret_cast<float *>(base + L.aabb));
         enqueue_boxes(sc, L, base, hdr, st);
@@ -604,7 +630,10 @@ hipError_t enqueue_build(const gr_scene &sc, const Layout &L, hipStream_t st) {
         float *aabb = reinterpret_cast<float *>(base + L.aabb);
         GaussRec32 *rec32 = reinterpret_cast<GaussRec32 *>(base + L.rec32);
         k_gather<<<blocks_for(n, 256), 256, 0, st>>>(sc.mean, sc.scale, sc.quat, sc.density, n,
-                                                      sc.kappa, v0, rec, rec32, cull, aabb);
+                                                      sc.kappa, L.leaf, v0, rec, rec32,
+                                                      base + L.axis,
+                                                      align256(size_t(n) * sizeof(AxisRec)), cull,
+                                                      aabb);
         if (L.n_leaves > 1) {
             Node *nodes = reinterpret_cast<Node *>(base + L.nodes);
             int32_t *lpar = reinterpret_cast<int32_t *>(base + L.lparent);

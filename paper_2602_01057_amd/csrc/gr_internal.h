@@ -27,6 +27,25 @@ struct alignas(16) GaussRec {
 };
 static_assert(sizeof(GaussRec) == 80, "GaussRec must be 80 bytes");
 
+// The same Gaussian as seen along coordinate axis k (80 bytes; t1, t2 the two
+// other axes, cyclic), for rays that are crossed by the planes of depth z along
+// k. In the plane z = mk + u the Gaussian's precision splits into a 2D part
+// about the conditional mean m + s u, whitened by the rows (l11, l21), (0, l22),
+// and h u^2 along the axis:
+//   x^T P x = (l11 f1 + l21 f2)^2 + (l22 f2)^2 + h u^2,  f_i = x_i - s_i u,
+// with s_i = Sigma_ik / Sigma_kk, h = 1 / Sigma_kk and (l11, l21, l22) the
+// Cholesky factor of P's (t1, t2) block. The projection reads one of a
+// Gaussian's three such records per packet.
+struct alignas(16) AxisRec {
+    double m1, m2, mk;
+    double s1, s2;
+    double l11, l21, l22;
+    double h;
+    float rho_c;  // rho sqrt(2 pi)
+    float pad;
+};
+static_assert(sizeof(AxisRec) == 80, "AxisRec must be 80 bytes");
+
 // Compact FP32 record of the same Gaussian (64 bytes, one scalar load), for
 // the forward's FP32 precision mode:
 //   mu   : the FP32 mean
@@ -82,7 +101,7 @@ struct Layout {
     int32_t level_count[kMaxLevels];
     int32_t level_off[kMaxLevels];
     int32_t wide_total;
-    size_t rec, rec32, cull, nodes, aabb, keys0, keys1, vals0, vals1, hist, lparent, visit, wbox, total;
+    size_t rec, rec32, axis, cull, nodes, aabb, keys0, keys1, vals0, vals1, hist, lparent, visit, wbox, total;
 };
 
 __device__ __host__ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -99,7 +118,8 @@ inline Layout make_layout(int64_t n, int32_t leaf) {
     size_t off = align256(sizeof(AccelHeader));
     L.rec = off;     off = align256(off + nn * sizeof(GaussRec));
     L.rec32 = off;   off = align256(off + nn * sizeof(GaussRec32));
-    L.cull = off;    off = align256(off + nn * kCullFields * sizeof(float));
+    L.axis = off;    off = off + 3 * align256(nn * sizeof(AxisRec));
+    L.cull = off;    off = align256(off + size_t(L.n_leaves) * leaf * kCullFields * sizeof(float));
     L.nodes = off;   off = align256(off + nodes * sizeof(Node));
     L.aabb = off;    off = align256(off + nn * 6 * sizeof(float));
     L.keys0 = off;   off = align256(off + nn * 4);
@@ -129,7 +149,7 @@ inline Layout make_layout(int64_t n, int32_t leaf) {
 struct SceneView {
     const AccelHeader *hdr;
     const GaussRec *rec;
-    const float *cull;  // kCullFields SoA arrays of length n
+    const float *cull;  // per leaf: kCullFields arrays of `leaf` floats
     const Node *nodes;
     const uint32_t *order;  // Morton position -> input index
     int64_t n;
@@ -149,6 +169,14 @@ __device__ __host__ inline const GaussRec32 *rec32_of(const SceneView &v) {
     const size_t nn = size_t(v.n > 0 ? v.n : 1);
     return reinterpret_cast<const GaussRec32 *>(reinterpret_cast<const char *>(v.rec) +
                                                 align256(nn * sizeof(GaussRec)));
+}
+
+// The axis records follow them, axis by axis.
+__device__ __host__ inline const AxisRec *axis_rec_of(const SceneView &v, int axis) {
+    const size_t nn = size_t(v.n > 0 ? v.n : 1);
+    return reinterpret_cast<const AxisRec *>(reinterpret_cast<const char *>(rec32_of(v)) +
+                                             align256(nn * sizeof(GaussRec32)) +
+                                             size_t(axis) * align256(nn * sizeof(AxisRec)));
 }
 
 // Error bits recorded in AccelHeader::flags by defensive device-side checks.

@@ -13,17 +13,17 @@
 //  3. at a leaf, up to 64 Gaussians are tested lane-parallel against the beam
 //     (the mean's offset at its depth against the beam's and the kappa
 //     ellipsoid's shadow's half widths), giving a 64-bit candidate mask;
-//  4. for each candidate the 80-byte Gaussian record is fetched with scalar
+//  4. for each candidate the 80-byte record of the run's axis is fetched with scalar
 //     loads and every lane evaluates the closed form for its ray.
 //
 // Closed form (Sec. 3.2-3.3, Eq. 7-11). With delta = o - mu, the literal
 // A = d^T P d, B = d^T P delta, C = delta^T P delta and D = C - B^2/A are
-// evaluated in FP64, which runs at the full non-packed FP32 rate on CDNA4:
-// delta is exact (FP32 inputs), and the cancellation of C A against B^2 costs
-// ~eps64 C/D relative, harmless even for origins hundreds of mm away. Only the
-// transcendentals run in FP32: r = rsqrt(A), D = (C A - B^2) r^2,
+// evaluated in FP64, which runs at the full non-packed FP32 rate on CDNA4, from
+// records of the Gaussians as seen along the run's axis (axis_core in
+// gr_trace.h: the same A and C A - B^2 as sums of squares, 21 operations). Only
+// the transcendentals run in FP32: r = rsqrt(A), D = (C A - B^2) r^2,
 // T = rho sqrt(2 pi) r exp2(-D log2(e)/2) when D <= kappa^2; the per-ray sum
-// accumulates in FP64. A = P : (d d^T) uses per-ray products of d.
+// accumulates in FP64.
 //
 // Gradient (not in the paper; derived from Eq. 11): with t* = -B/A and
 // p = delta + t* d (the line's closest point to mu in the metric P),
@@ -55,20 +55,20 @@ namespace gr {
 // first evaluation (hold_records, as the recording loop of the fused pass
 // does) ran this kernel 4% slower: more scalar registers spill at 8 waves.
 template <bool kStats>
-__device__ inline void leaf_forward(const SceneView &S, const RayD &R, int64_t start, uint64_t mask,
-                                    float k2, double &acc, uint32_t &n_inc,
-                                    uint32_t &n_hitc) {
+__device__ inline void leaf_forward(const AxisRec *rec, const RunRay &Q, int64_t start, uint64_t mask,
+                                    double &acc, uint32_t &n_inc, uint32_t &n_hitc) {
+    const float k2 = Q.cut;
     while (mask) {
         const int j0 = __builtin_ctzll(mask);
         mask &= mask - 1;
         const bool two = mask != 0;
         const int j1 = two ? __builtin_ctzll(mask) : j0;
         if (two) mask &= mask - 1;
-        const GaussRec G0 = sload(S.rec, start + j0);
-        const GaussRec G1 = sload(S.rec, start + j1);
-        PairCore c;
+        const AxisRec G0 = sload(rec, start + j0);
+        const AxisRec G1 = sload(rec, start + j1);
+        AxisCore c;
         float D, r;
-        pair_core(G0.mu, G0.P, R.o, R.d, R.dd, c);
+        axis_core(G0, Q, c);
         pair_D(c, D, r);
         if (kStats) n_hitc += ballot(D <= k2) != 0 ? 1u : 0u;
         if (D <= k2) {
@@ -76,7 +76,7 @@ __device__ inline void leaf_forward(const SceneView &S, const RayD &R, int64_t s
             if (kStats) ++n_inc;
         }
         if (two) {
-            pair_core(G1.mu, G1.P, R.o, R.d, R.dd, c);
+            axis_core(G1, Q, c);
             pair_D(c, D, r);
             if (kStats) n_hitc += ballot(D <= k2) != 0 ? 1u : 0u;
             if (D <= k2) {
@@ -166,19 +166,17 @@ __device__ inline void packet_forward(const LaunchTable &T, int64_t packet, int 
     double acc = 0.0;
     uint32_t n_inc = 0, n_cand = 0, n_leaf = 0, n_hitc = 0;
     const float inv_dd = kCompact ? 1.0f / (R.d[0] * R.d[0] + R.d[1] * R.d[1] + R.d[2] * R.d[2]) : 0.0f;
-    traverse_runs(T.traversal, S, R, ballot(P.active), lane, stack, [&](int l, bool in, const RayD &Q, const Beam &B) {
+    traverse_runs(T.traversal, S, R, ballot(P.active), lane, stack, [&](int l, const RunRay &Q, const Beam &B) {
         int64_t start;
         const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-        // lanes outside the run compare against a cutoff that no D >= 0 passes
-        const float k2 = in ? S.kappa2 : -1.0f;
         if (kStats) {
             ++n_leaf;
             n_cand += __builtin_popcountll(mask);
         }
         if constexpr (kCompact)
-            leaf_forward32<kStats>(S, R, inv_dd, start, mask, k2, acc, n_inc, n_hitc);
+            leaf_forward32<kStats>(S, R, inv_dd, start, mask, Q.cut, acc, n_inc, n_hitc);
         else
-            leaf_forward<kStats>(S, Q, start, mask, k2, acc, n_inc, n_hitc);
+            leaf_forward<kStats>(B.rec, Q, start, mask, acc, n_inc, n_hitc);
     });
     if (P.active) out[P.out] = float(acc);
     if (kStats) {
@@ -207,15 +205,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     uint32_t *stack = fwd_stack + wave * kWideStack;
-    if (T.work_counter) {
-        // persistent: waves pull packets until the table is exhausted
-        for (int64_t packet = next_packet(T.work_counter, lane); packet < T.n_packets;
-             packet = next_packet(T.work_counter, lane))
-            packet_forward<kStats, kCompact>(T, packet, lane, stack, stats);
-        return;
+    // persistent: waves pull packets until the table is exhausted
+    const bool pull = T.work_counter != nullptr;
+    int64_t packet = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
+    while (packet < T.n_packets) {
+        packet_forward<kStats, kCompact>(T, packet, lane, stack, stats);
+        packet = pull ? next_packet(T.work_counter, lane) : T.n_packets;
     }
-    const int64_t packet = logical_block(T.xcd_remap) * T.waves_per_group + wave;
-    packet_forward<kStats, kCompact>(T, packet, lane, stack, stats);
 }
 
 // Per-ray record staged in LDS for the backward (56 bytes: a stride of 14
@@ -445,20 +441,21 @@ struct HitList {
 
 // Forward sum over one leaf's candidates (as leaf_forward), also recording the
 // packet's hit list.
-__device__ inline void leaf_forward_hits(const SceneView &S, const RayD &R, int64_t start, uint64_t mask,
-                                         float k2a, double &acc, HitList &H, int lane) {
+__device__ inline void leaf_forward_hits(const AxisRec *rec, const RunRay &Q, int64_t start, uint64_t mask,
+                                         double &acc, HitList &H, int lane) {
+    const float k2a = Q.cut;
     while (mask) {
         const int j0 = __builtin_ctzll(mask);
         mask &= mask - 1;
         const bool two = mask != 0;
         const int j1 = two ? __builtin_ctzll(mask) : j0;
         if (two) mask &= mask - 1;
-        const GaussRec G0 = sload(S.rec, start + j0);
-        const GaussRec G1 = sload(S.rec, start + j1);
+        const AxisRec G0 = sload(rec, start + j0);
+        const AxisRec G1 = sload(rec, start + j1);
         hold_records(G0, G1);
-        PairCore c;
+        AxisCore c;
         float D, r;
-        pair_core(G0.mu, G0.P, R.o, R.d, R.dd, c);
+        axis_core(G0, Q, c);
         pair_D(c, D, r);
         const uint64_t h0 = __builtin_amdgcn_ballot_w64(D <= k2a);
         if (h0) {
@@ -469,7 +466,7 @@ __device__ inline void leaf_forward_hits(const SceneView &S, const RayD &R, int6
             H.record(lane, start + j0, h0);
         }
         if (two) {
-            pair_core(G1.mu, G1.P, R.o, R.d, R.dd, c);
+            axis_core(G1, Q, c);
             pair_D(c, D, r);
             const uint64_t h1 = __builtin_amdgcn_ballot_w64(D <= k2a);
             if (h1) {
@@ -607,11 +604,11 @@ __device__ inline void retraverse_backward(const LaunchTable &T, const SceneView
                                            const Rays &rays, uint64_t live_mask, int lane, float k2, float *acc) {
     int count = 0;        // wave-uniform number of listed candidates
     uint64_t listed = 0;  // the rays they are for
-    traverse_runs(T.traversal, S, R, live_mask, lane, Lt.stack, [&](int l, bool in, const RayD &Q, const Beam &B) {
+    traverse_runs(T.traversal, S, R, live_mask, lane, Lt.stack, [&](int l, const RunRay &Q, const Beam &B) {
         int64_t start;
         const uint64_t mask = leaf_candidates(S, B, l, lane, start);
         if (!mask) return;
-        const uint64_t run = ballot(in);
+        const uint64_t run = ballot(Q.cut >= 0.0f);
         if (run != listed) {
             if (count > 0) backward_batch(S, Lt, rays, count, listed, lane, k2, acc);
             __builtin_amdgcn_wave_barrier();
@@ -658,20 +655,20 @@ __device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int
         double sum = 0.0;
         if (T.hit_cap > 0 && hit_g) {
             HitList H{hit_g, hit_m, T.hit_cap, 0, 0, false, 0u, 0u, 0u};
-            traverse_runs(T.traversal, S, R, ballot(P.active), lane, L->t.stack, [&](int l, bool in, const RayD &Q, const Beam &B) {
+            traverse_runs(T.traversal, S, R, ballot(P.active), lane, L->t.stack, [&](int l, const RunRay &Q, const Beam &B) {
                 int64_t start;
                 const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-                leaf_forward_hits(S, Q, start, mask, in ? k2 : -1.0f, sum, H, lane);
+                leaf_forward_hits(B.rec, Q, start, mask, sum, H, lane);
             });
             H.flush(lane);
             listed = !H.overflow;
             n_ent = H.n;
         } else {
             uint32_t dummy = 0, dummy2 = 0;
-            traverse_runs(T.traversal, S, R, ballot(P.active), lane, L->t.stack, [&](int l, bool in, const RayD &Q, const Beam &B) {
+            traverse_runs(T.traversal, S, R, ballot(P.active), lane, L->t.stack, [&](int l, const RunRay &Q, const Beam &B) {
                 int64_t start;
                 const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-                leaf_forward<false>(S, Q, start, mask, in ? k2 : -1.0f, sum, dummy, dummy2);
+                leaf_forward<false>(B.rec, Q, start, mask, sum, dummy, dummy2);
             });
         }
         const float I = float(sum);
@@ -736,18 +733,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     WaveLdsOf<kFused> *L = reinterpret_cast<WaveLdsOf<kFused> *>(lds_raw) + wave;
-    if (T.work_counter) {
-        // hit-list regions belong to persistent waves (one per wave slot)
-        const int64_t slot = int64_t(blockIdx.x) * T.waves_per_group + wave;
-        uint32_t *hg = T.hit_cap > 0 ? T.hit_g + slot * T.hit_cap : nullptr;
-        uint64_t *hm = T.hit_cap > 0 ? T.hit_m + slot * T.hit_cap : nullptr;
-        for (int64_t packet = next_packet(T.work_counter, lane); packet < T.n_packets;
-             packet = next_packet(T.work_counter, lane))
-            packet_backward<kFused>(T, packet, lane, L, A, hg, hm);
-        return;
+    const bool pull = T.work_counter != nullptr;
+    // hit-list regions belong to persistent waves (one per wave slot)
+    const int64_t slot = int64_t(blockIdx.x) * T.waves_per_group + wave;
+    const bool lists = pull && T.hit_cap > 0;
+    uint32_t *hg = lists ? T.hit_g + slot * T.hit_cap : nullptr;
+    uint64_t *hm = lists ? T.hit_m + slot * T.hit_cap : nullptr;
+    int64_t packet = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
+    while (packet < T.n_packets) {
+        packet_backward<kFused>(T, packet, lane, L, A, hg, hm);
+        packet = pull ? next_packet(T.work_counter, lane) : T.n_packets;
     }
-    const int64_t packet = logical_block(T.xcd_remap) * T.waves_per_group + wave;
-    packet_backward<kFused>(T, packet, lane, L, A, nullptr, nullptr);
 }
 
 // Zero the accumulators (a fill kernel, so the call stays capturable).

@@ -359,11 +359,14 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
     Ray R;
     load_ray(sg.ro, sg.rd, sg.stride, P.ray, R);
     Beam B;
-    const uint64_t run = S.n > 0 ? next_run(E, R, todo, lane, B) : (todo = 0);
+    RunRay V;
+    const uint64_t run = S.n > 0 ? next_run(E, R, todo, lane, B, V) : (todo = 0);
     if (!run) continue;
     lines |= run;
     const bool in = (run >> lane) & 1ull;
-    const RayD V = widen_ray(R);
+    const AxisRec *rec = axis_rec_of(S, B.ax);
+    // parameter of the line where it crosses the plane of depth z: z it - ot
+    const double it = 1.0 / V.dk, ot = double(pick(R.o, B.ax)) * it;
     const float k2 = in ? S.kappa2 : -1.0f;
     double acc[kBins];
 #pragma unroll
@@ -379,10 +382,10 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
         }
     };
     // the cutoff test of one candidate; a pair inside it is queued
-    auto pair_in = [&](const GaussRec &G) __attribute__((always_inline)) {
-        PairCore c;
+    auto pair_in = [&](const AxisRec &G) __attribute__((always_inline)) {
+        AxisCore c;
         float D, r;
-        pair_core(G.mu, G.P, V.o, V.d, V.dd, c);
+        axis_core(G, V, c);
         pair_D(c, D, r);
         if (D <= k2) {
             const float Tv = G.rho_c * r * gauss_exp(D);
@@ -394,7 +397,7 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
                 ra = fma(ra, fma(-c.A, ra, 1.0), ra);
                 const int slot = (head + cnt) & (kTofQ - 1);
                 Q.ra[slot][lane] = ra;
-                Q.tn[slot][lane] = c.B * ra;
+                Q.tn[slot][lane] = fma(fma(c.a, c.c, c.b * c.d), ra, fma(-G.mk, it, ot));
                 Q.tv[slot][lane] = Tv;
                 ++cnt;
             }
@@ -410,8 +413,8 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
             const bool two = mask != 0;
             const int j1 = two ? __builtin_ctzll(mask) : j0;
             if (two) mask &= mask - 1;
-            const GaussRec G0 = sload(S.rec, start + j0);
-            const GaussRec G1 = sload(S.rec, start + j1);
+            const AxisRec G0 = sload(rec, start + j0);
+            const AxisRec G1 = sload(rec, start + j1);
             hold_records(G0, G1);
             pair_in(G0);
             if (two) pair_in(G1);
@@ -455,14 +458,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kBins > 16 
     unsigned char *base = tof_lds + size_t(wave) * (sizeof(TofQueue) + sizeof(uint32_t) * kWideStack);
     TofQueue &Q = *reinterpret_cast<TofQueue *>(base);
     uint32_t *stack = reinterpret_cast<uint32_t *>(base + sizeof(TofQueue));
-    if (T.work_counter) {
-        for (int64_t packet = next_packet(T.work_counter, lane); packet < T.n_packets;
-             packet = next_packet(T.work_counter, lane))
-            packet_forward_tof<kBins>(T, A, packet, lane, stack, Q);
-        return;
+    const bool pull = T.work_counter != nullptr;
+    int64_t packet = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
+    while (packet < T.n_packets) {
+        packet_forward_tof<kBins>(T, A, packet, lane, stack, Q);
+        packet = pull ? next_packet(T.work_counter, lane) : T.n_packets;
     }
-    const int64_t packet = logical_block(T.xcd_remap) * T.waves_per_group + wave;
-    packet_forward_tof<kBins>(T, A, packet, lane, stack, Q);
 }
 
 // Gradient sums of one (ray, Gaussian) pair with the ray's bin weights wi[64 b].
@@ -639,27 +640,28 @@ __device__ inline void packet_backward_tof(const LaunchTable &T, const TofArgs &
     mine.c = ray_center(A, P.ray);
     float *acc = A.acc;
     TofPending pe{0, 0u, 0ull};
-    traverse_runs(T.traversal, S, R, ballot(live), lane, L.stack, [&](int l, bool in, const RayD &V, const Beam &B) {
+    traverse_runs(T.traversal, S, R, ballot(live), lane, L.stack, [&](int l, const RunRay &V, const Beam &B) {
         int64_t start;
         uint64_t mask = leaf_candidates(S, B, l, lane, start);
-        const float k2r = in ? k2 : -1.0f;
+        const float k2r = V.cut;
+        const AxisRec *rec = B.rec;
         while (mask) {
             const int j0 = __builtin_ctzll(mask);
             mask &= mask - 1;
             const bool two = mask != 0;
             const int j1 = two ? __builtin_ctzll(mask) : j0;
             if (two) mask &= mask - 1;
-            const GaussRec G0 = sload(S.rec, start + j0);
-            const GaussRec G1 = sload(S.rec, start + j1);
+            const AxisRec G0 = sload(rec, start + j0);
+            const AxisRec G1 = sload(rec, start + j1);
             hold_records(G0, G1);
-            PairCore c;
+            AxisCore c;
             float D, r;
-            pair_core(G0.mu, G0.P, V.o, V.d, V.dd, c);
+            axis_core(G0, V, c);
             pair_D(c, D, r);
             const uint64_t h0 = ballot(D <= k2r);
             if (h0) pe.put(lane, start + j0, h0);
             if (two) {
-                pair_core(G1.mu, G1.P, V.o, V.d, V.dd, c);
+                axis_core(G1, V, c);
                 pair_D(c, D, r);
                 const uint64_t h1 = ballot(D <= k2r);
                 if (h1) pe.put(lane, start + j1, h1);
@@ -679,14 +681,12 @@ __global__ __launch_bounds__(256) void k_backward_tof(LaunchTable T, TofArgs A) 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const TofWave<TofWinB> L = tof_wave<TofWinB>(tof_lds, wave, tof_rows(A.n_bins > 0 ? A.n_bins : 1));
-    if (T.work_counter) {
-        for (int64_t packet = next_packet(T.work_counter, lane); packet < T.n_packets;
-             packet = next_packet(T.work_counter, lane))
-            packet_backward_tof<kBins>(T, A, packet, lane, L);
-        return;
+    const bool pull = T.work_counter != nullptr;
+    int64_t packet = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
+    while (packet < T.n_packets) {
+        packet_backward_tof<kBins>(T, A, packet, lane, L);
+        packet = pull ? next_packet(T.work_counter, lane) : T.n_packets;
     }
-    const int64_t packet = logical_block(T.xcd_remap) * T.waves_per_group + wave;
-    packet_backward_tof<kBins>(T, A, packet, lane, L);
 }
 
 // TOF centre of each ray: the parameter where it passes closest to the z axis

@@ -153,10 +153,10 @@ __global__ __launch_bounds__(256) void k_voxelize(SceneView S, VoxGrid G, float 
                 bool cand = false;
                 if (lane < gc) {
                     const int64_t g = start + lane;
-                    const float mu[3] = {S.cull[g], S.cull[S.n + g], S.cull[2 * S.n + g]};
-                    const float h[3] = {sqrtf(fmaxf(S.cull[3 * S.n + g], 0.0f)),
-                                        sqrtf(fmaxf(S.cull[4 * S.n + g], 0.0f)),
-                                        sqrtf(fmaxf(S.cull[5 * S.n + g], 0.0f))};
+                    const float *c = S.cull + start * kCullFields + lane;
+                    const float mu[3] = {c[0], c[S.leaf], c[2 * S.leaf]};
+                    const float h[3] = {sqrtf(fmaxf(c[3 * S.leaf], 0.0f)), sqrtf(fmaxf(c[4 * S.leaf], 0.0f)),
+                                        sqrtf(fmaxf(c[5 * S.leaf], 0.0f))};
                     float lo[3], hi[3];
                     for (int k = 0; k < 3; ++k) {
                         lo[k] = mu[k] - h[k];
