@@ -33,13 +33,10 @@
 //   g_rho = sum w T/rho, m = sum w T p, M = sum w T (p p^T + d d^T / A)
 // (10 floats) and adds them to the Gaussian's accumulators with float
 // atomics; k_epilogue maps them to mean, scale and quaternion gradients. The
-// fused pass records each packet's (Gaussian, ray mask) hit list in its forward
+// fused pass records each run's (Gaussian, ray mask) hit list in its forward
 // half and replays it with the pairs spread evenly over the lanes; with dL/dI
-// given, or for a list that outgrew its region, the backward re-traverses and
-// runs Gaussian-major (candidates one per lane, each looping over the packet's
-// weighted rays).
-#include <type_traits>
-
+// given, or for a list that outgrew its region, the traversal runs again with
+// the cutoff test alone and its hits are replayed window by window.
 #include "gr_trace.h"
 
 namespace gr {
@@ -214,79 +211,42 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     }
 }
 
-// Per-ray record staged in LDS for the backward (56 bytes: a stride of 14
-// dwords spreads the rays of a packet over the LDS banks when lanes gather
-// different rays). d d^T is recomputed from d where needed.
-struct RayRec {
-    double o[3];
-    double d[3];
-    float w;        // dL/dI of the ray
-    float pad;
-};
-static_assert(sizeof(RayRec) == 56, "RayRec must be 56 bytes");
-
-// A ray as its lane holds it for the backward: the FP32 inputs (exact in
-// FP64) and the weight dL/dI.
-struct RayF {
-    float o[3], d[3];
+// A ray as its lane holds it for the replay of its run: the line across the
+// run's axis and the weight dL/dI over |dk|, which makes the direction (S1, S2, 1).
+struct ReplayRay {
+    double X1, X2, S1, S2;
     float w;
 };
 
-__device__ inline RayRec widen(const RayF &f) {
-    RayRec r;
-    for (int k = 0; k < 3; ++k) {
-        r.o[k] = double(f.o[k]);
-        r.d[k] = double(f.d[k]);
-    }
-    r.w = f.w;
-    r.pad = 0.0f;
-    return r;
+__device__ inline double gather_f64(double v, int byte) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = uint32_t(__builtin_amdgcn_ds_bpermute(byte, int(uint32_t(u))));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_ds_bpermute(byte, int(uint32_t(u >> 32))));
+    return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
 }
 
 // Ray i from the lane that holds it (ds_bpermute; every lane of the wave must
 // execute this). i is per lane.
-__device__ inline RayRec gather_ray(const RayF &mine, int i) {
+__device__ inline ReplayRay gather_ray(const ReplayRay &mine, int i) {
     const int a = i << 2;
-    auto g = [&](float v) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(a, __builtin_bit_cast(int, v)));
-    };
-    RayF f;
-    for (int k = 0; k < 3; ++k) {
-        f.o[k] = g(mine.o[k]);
-        f.d[k] = g(mine.d[k]);
-    }
-    f.w = g(mine.w);
-    return widen(f);
+    ReplayRay r;
+    r.X1 = gather_f64(mine.X1, a);
+    r.X2 = gather_f64(mine.X2, a);
+    r.S1 = gather_f64(mine.S1, a);
+    r.S2 = gather_f64(mine.S2, a);
+    r.w = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(a, __builtin_bit_cast(int, mine.w)));
+    return r;
 }
 
-// Ray i, the same on every lane (v_readlane into scalars).
-__device__ inline RayRec lane_ray(const RayF &mine, int i) {
-    auto r = [&](float v) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), i));
-    };
-    RayF f;
-    for (int k = 0; k < 3; ++k) {
-        f.o[k] = r(mine.o[k]);
-        f.d[k] = r(mine.d[k]);
-    }
-    f.w = r(mine.w);
-    return widen(f);
-}
-
-constexpr int kCandCap = 128;  // candidate list slots per wave (a batch is 64)
-
-// One window of up to kWin hit-list entries being replayed (non-empty ones
-// only, in list order): records, masks, Gaussian indices, inclusive prefix
-// sums of the pair counts, and the per-entry gradient sums (SoA,
-// res[k][entry]). 64 entries take 8.5 KB per wave, so the 160 KB of a compute
-// unit hold 18 waves' windows, against the 20 that the fused kernel's
-// registers allow.
-constexpr int kWin = 64;
-constexpr int kWinLog2 = 6;  // search steps: 2^6 >= kWin
+// One window of up to kWin hit entries being replayed (non-empty ones only, in
+// list order): the run's axis records, masks, Gaussian indices, inclusive
+// prefix sums of the pair counts, and the per-entry gradient sums (SoA,
+// res[k][entry]).
+template <int kWin>
 struct HitWindow {
     union {
-        GaussRec rec[kWin];
-        float part[10][kWin];  // lanes' closing sums, once the window's pairs are done
+        AxisRec rec[kWin];
+        float part[10][64];  // lanes' closing sums, once the window's pairs are done
     };
     float res[10][kWin];
     uint64_t m[kWin];
@@ -294,103 +254,85 @@ struct HitWindow {
     int32_t incl[kWin];
 };
 
-// Traversal stack and candidate list of the re-traversal backward.
+// The replay of a recorded list takes windows of 64 entries: 8.5 KB per wave,
+// so the 160 KB of a compute unit hold 18 waves' windows, against the 20 that
+// the fused kernel's registers allow. During a re-traversal the traversal
+// stack is live as well: 48 entries and the stack take 7.6 KB.
+constexpr int kListWin = 64, kTravWin = 48;
+
 struct TravLds {
-    int32_t cand[kCandCap];
+    HitWindow<kTravWin> win;
     uint32_t stack[kWideStack];
 };
 
-// Per-wave LDS of the fused kernel: the rays stay in their lanes (gathered
-// with bpermute / readlane), so the whole budget goes to the replay window.
-struct WaveLdsFused {
-    union {
-        TravLds t;      // traversal and re-traversal backward
-        HitWindow win;  // hit-list replay (the traversal is over by then)
-    };
-};
-
-// Per-wave LDS of the backward with dL/dI given: the weighted rays staged at
-// their lane's slot, read by all lanes at once in the Gaussian-major batches.
-struct WaveLdsPlain {
-    RayRec rays[64];
+// Per-wave LDS of the backward kernels.
+union WaveLds {
     TravLds t;
+    HitWindow<kListWin> win;  // hit-list replay (the traversal is over by then)
 };
 
-// Where a batch reads ray i from (i is the same on every lane).
-struct RaysInLds {
-    const RayRec *rays;
-    __device__ RayRec get(int i) const { return rays[i]; }
-};
-struct RaysInLanes {
-    const RayF &mine;
-    __device__ RayRec get(int i) const { return lane_ray(mine, i); }
-};
-
-// Gradient terms of one (ray, Gaussian) pair added to the ten accumulators
-// c = (sum w E, sum wT p, sum of the symmetric wT (p p^T + d d^T / A)) that the
-// epilogue turns into parameter gradients; E is the unit-density integral
-// sqrt(2 pi / A) exp(-D/2) and T = rho E. Returns whether the pair is inside
-// the cutoff (D <= kappa^2).
-__device__ inline bool pair_grad(const double mu[3], const double P[6], float rho, const RayRec &Rr, float k2,
-                                 float c[10]) {
-    double dd[6];
-    ray_dd(Rr.d, dd);
-    PairCore pc;
-    pair_core(mu, P, Rr.o, Rr.d, dd, pc);
-    float D, r;
-    pair_D(pc, D, r);
-    if (!(D <= k2)) return false;
-    // p = delta - (B/A) d in FP64 (t = B/A can be hundreds of mm);
+// Gradient terms of one included (ray, Gaussian) pair added to the ten sums
+// c = (sum w E, sum wT p, sum of the symmetric wT (p p^T + d d^T / A)), E the
+// unit-density integral sqrt(2 pi / A) exp(-D/2), T = rho E, and p the line's
+// closest point to the mean in the metric P. Vectors are in the record's
+// whitened frame (a, b, u) (AxisRec): the offset is (a, b, 0), the direction
+// (c, d, 1), p = (a + t c, b + t d, t) with t = -B/A, and D = |p|^2 there. The
+// whitened sums round with each axis' own size, so a flat Gaussian's short
+// axis keeps its digits; unwhiten_sums maps them to coordinates per window.
+__device__ inline void pair_grad(const AxisRec &G, float rho, float h, const ReplayRay &R, float c[10]) {
+    const double e1 = fma(G.mk, R.S1, R.X1 - G.m1), e2 = fma(G.mk, R.S2, R.X2 - G.m2);
+    const double g1 = R.S1 - G.s1, g2 = R.S2 - G.s2;
+    const double a = fma(G.l21, e2, G.l11 * e1), b = G.l22 * e2;
+    const double cc = fma(G.l21, g2, G.l11 * g1), dd = G.l22 * g2;
+    const double A = fma(dd, dd, fma(cc, cc, G.h));
+    const float r = __builtin_amdgcn_rsqf(float(A));
     // 1/A from the FP32 r^2 (relative error ~1e-7) and one Newton step
     double ra = double(r * r);
-    ra = fma(ra, fma(-pc.A, ra, 1.0), ra);
-    const double t = pc.B * ra;
-    const float p0 = float(fma(-t, Rr.d[0], pc.dl[0]));
-    const float p1 = float(fma(-t, Rr.d[1], pc.dl[1]));
-    const float p2 = float(fma(-t, Rr.d[2], pc.dl[2]));
-    const float wE = Rr.w * (kSqrt2Pi * r * gauss_exp(D));
+    ra = fma(ra, fma(-A, ra, 1.0), ra);
+    const double t = -fma(a, cc, b * dd) * ra;
+    const float p0 = float(fma(t, cc, a)), p1 = float(fma(t, dd, b)), p2 = float(t);
+    const float f0 = float(cc), f1 = float(dd);
+    const float D = fmaf(p0, p0, fmaf(p1, p1, h * (p2 * p2)));
+    const float wE = R.w * (kSqrt2Pi * r * gauss_exp(D));
     const float wT = wE * rho;
     const float wTA = wT * (r * r);
     const float q0 = wT * p0, q1 = wT * p1, q2 = wT * p2;
-    const float f0 = float(Rr.d[0]), f1 = float(Rr.d[1]), f2 = float(Rr.d[2]);  // exact (FP32 input)
-    const float v0 = wTA * f0, v1 = wTA * f1, v2 = wTA * f2;
+    const float v0 = wTA * f0, v1 = wTA * f1;
     c[0] += wE;
     c[1] += q0;
     c[2] += q1;
     c[3] += q2;
     c[4] = fmaf(q0, p0, fmaf(v0, f0, c[4]));
     c[5] = fmaf(q1, p1, fmaf(v1, f1, c[5]));
-    c[6] = fmaf(q2, p2, fmaf(v2, f2, c[6]));
+    c[6] = fmaf(q2, p2, wTA + c[6]);
     c[7] = fmaf(q0, p1, fmaf(v0, f1, c[7]));
-    c[8] = fmaf(q0, p2, fmaf(v0, f2, c[8]));
-    c[9] = fmaf(q1, p2, fmaf(v1, f2, c[9]));
-    return true;
+    c[8] = fmaf(q0, p2, v0 + c[8]);
+    c[9] = fmaf(q1, p2, v1 + c[9]);
 }
 
-__device__ inline void flush_grad(float *acc, int64_t n, int64_t g, float c[10]) {
-    for (int k = 0; k < 10; ++k) {
-        atomicAdd(&acc[k * n + g], c[k]);
-        c[k] = 0.0f;
-    }
-}
-
-// One batch of up to 64 candidate Gaussians (lane j owns cand[j]) against the
-// packet's staged rays (the set bits of live).
-template <class Rays>
-__device__ inline void backward_batch(const SceneView &S, const TravLds &Lt, const Rays &rays, int cnt,
-                                      uint64_t live, int lane, float k2, float *acc) {
-    const bool own = lane < cnt;
-    const int64_t g = own ? Lt.cand[lane] : Lt.cand[0];
-    const GaussRec G = S.rec[g];
-    const float rho = G.rho_c * (1.0f / kSqrt2Pi);
-    float c[10];
-    for (int k = 0; k < 10; ++k) c[k] = 0.0f;
-    bool any = false;
-    for (uint64_t lm = live; lm; lm &= lm - 1) {
-        const int i = __builtin_ctzll(lm);
-        any |= pair_grad(G.mu, G.P, rho, rays.get(i), k2, c);
-    }
-    if (own && any) flush_grad(acc, S.n, g, c);
+// The ten sums of one Gaussian added to its accumulators, from the whitened
+// frame to coordinates: x1 = a / l11 - l21 b / (l11 l22) + s1 u,
+// x2 = b / l22 + s2 u, xk = u, with (x1, x2, xk) along (t1, t2, ax).
+__device__ inline void unwhiten_sums(const AxisRec &G, int ax, const float c[10], float *acc, int64_t n, int64_t g) {
+    const int t1 = ax == 2 ? 0 : ax + 1, t2 = ax == 0 ? 2 : ax - 1;
+    const double i11 = 1.0 / G.l11, i22 = 1.0 / G.l22, i12 = -G.l21 * i11 * i22;
+    const double m0 = c[1], m1 = c[2], m2 = c[3];
+    const double Maa = c[4], Mbb = c[5], Muu = c[6], Mab = c[7], Mau = c[8], Mbu = c[9];
+    // rows of T M for T = [[i11, i12, s1], [0, i22, s2], [0, 0, 1]]
+    const double ra = fma(G.s1, Mau, fma(i12, Mab, i11 * Maa)), rb = fma(G.s1, Mbu, fma(i12, Mbb, i11 * Mab)),
+                 ru = fma(G.s1, Muu, fma(i12, Mbu, i11 * Mau));
+    const double sb = fma(G.s2, Mbu, i22 * Mbb), su = fma(G.s2, Muu, i22 * Mbu);
+    auto add = [&](int row, double v) { atomicAdd(&acc[row * n + g], float(v)); };
+    add(0, double(c[0]));
+    add(1 + t1, fma(G.s1, m2, fma(i12, m1, i11 * m0)));
+    add(1 + t2, fma(G.s2, m2, i22 * m1));
+    add(1 + ax, m2);
+    add(4 + t1, fma(G.s1, ru, fma(i12, rb, i11 * ra)));
+    add(4 + t2, fma(G.s2, su, i22 * sb));
+    add(4 + ax, Muu);
+    add(6 + t1 + t2, fma(G.s2, ru, i22 * rb));  // xy, xz, yz at 7, 8, 9
+    add(6 + t1 + ax, ru);
+    add(6 + t2 + ax, su);
 }
 
 // v_writelane_b32: returns old with lane `lane` replaced by the wave-uniform
@@ -480,106 +422,113 @@ __device__ inline void leaf_forward_hits(const AxisRec *rec, const RunRay &Q, in
     }
 }
 
-// Backward half from a recorded hit list, in windows of kWin entries. The T
-// included pairs of a window are split evenly over the lanes (lane k takes
-// pairs [k s, k s + s) of the window's pairs in list order, s = ceil(T / 64)),
-// so every lane is busy however unequal the entries' ray counts are. A lane
-// that moves on from an entry stores its sums into the window's LDS slot for
-// it; the sums for the entry it is in when its range ends are added per run
-// of lanes ending in that entry, with no LDS atomics. At the end of the
-// window lane j adds entry j's sums to the global
-// accumulators, so those atomics cover consecutive Gaussians of the same
-// leaves. The next window's entries are loaded while the current window runs.
-__device__ inline void drain_hits(const SceneView &S, WaveLdsFused *L, const RayF &mine, const uint32_t *hg,
-                                  const uint64_t *hm, int n_ent, uint64_t live, int lane, float k2,
-                                  float *acc) {
-    const int64_t n = S.n;
-    HitWindow &W = L->win;
+// One window of a run's hit entries: lane j holds entry j (Gaussian gj, mask mj
+// of its rays; 0 = none). The T included pairs of the window are split evenly
+// over the lanes (lane k takes pairs [k s, k s + s) in list order,
+// s = ceil(T / 64)), so every lane is busy however unequal the entries' ray
+// counts are. A lane that moves on from an entry stores its sums into the
+// window's LDS slot for it; the sums for the entry it is in when its range ends
+// are added per run of lanes ending in that entry, with no LDS atomics. At the
+// end of the window lane j adds entry j's sums to the global accumulators, so
+// those atomics cover consecutive Gaussians of the same leaves.
+template <int kWin>
+__device__ inline void replay_window(const AxisRec *rec, int ax, int64_t n, HitWindow<kWin> &W, int64_t gj,
+                                     uint64_t mj, const ReplayRay &mine, int lane, float *acc) {
     const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-    // entries (pg, pm) of the next window, in flight
+    const int cj = __builtin_popcountll(mj);
+    const int incl = wave_incl_scan(cj);
+    const int T = __builtin_amdgcn_readlane(incl, 63);
+    if (T == 0) return;
+    // compact the entries with pairs into slots 0..nq-1
+    const uint64_t nonempty = ballot(cj > 0);
+    const int nq = __builtin_popcountll(nonempty);
+    if (cj > 0) {
+        const int q = __builtin_popcountll(nonempty & below);
+        W.rec[q] = rec[gj];
+        W.m[q] = mj;
+        W.g[q] = int32_t(gj);
+        W.incl[q] = incl;
+    }
+    if (lane < kWin)
+        for (int k = 0; k < 10; ++k) W.res[k][lane] = 0.0f;
+    __builtin_amdgcn_wave_barrier();
+    const int inclq = lane < nq ? W.incl[lane] : T;
+    // this lane's pairs: [p, p + left) of the window's T pairs
+    const int s = (T + 63) >> 6;
+    const int p = lane * s;
+    const int left = max(0, min(s, T - p));
+    // first slot whose inclusive count exceeds p (binary search over lanes)
+    int lo = 0, hi = 63;
+    for (int step = 0; step < 6; ++step) {
+        const int mid = (lo + hi) >> 1;
+        const int v = __shfl(inclq, mid, 64);
+        if (v > p) hi = mid; else lo = mid + 1;
+    }
+    int e = left > 0 ? lo : 0;
+    uint64_t m = W.m[e];
+    // skip the entry's first (p - exclusive prefix) rays
+    if (left > 0) m = drop_low_bits(m, p - (W.incl[e] - __builtin_popcountll(m)));
+    AxisRec G = W.rec[e];
+    float rho = G.rho_c * (1.0f / kSqrt2Pi), h = float(G.h);
+    float c[10];
+    for (int k = 0; k < 10; ++k) c[k] = 0.0f;
+    for (int it = 0; it < s; ++it) {
+        const bool act = it < left;
+        if (act && m == 0) {
+            // Entry e ends inside this lane's range, so no other lane
+            // leaves it inside the loop: the lanes that also hold part of
+            // it hold its start and add their sums after the loop. Its
+            // slot is still zero here, and a plain store replaces the
+            // LDS float atomic.
+            for (int k = 0; k < 10; ++k) {
+                W.res[k][e] = c[k];
+                c[k] = 0.0f;
+            }
+            e = min(e + 1, nq - 1);
+            m = W.m[e];
+            G = W.rec[e];
+            rho = G.rho_c * (1.0f / kSqrt2Pi);
+            h = float(G.h);
+        }
+        // the gather runs on every lane (bpermute needs its sources active)
+        const int i = act ? __builtin_ctzll(m) : lane;
+        const ReplayRay Rr = gather_ray(mine, i);
+        if (act) {
+            m &= m - 1;
+            pair_grad(G, rho, h, Rr, c);
+        }
+    }
+    // the closing sums take the records' place: each lane keeps its own entry's
+    const AxisRec Gq = W.rec[min(lane, nq - 1)];
+    close_window<kWin>(W.part, W.res, c, left > 0 ? e : -1, lane);
+    if (lane < nq) {
+        for (int k = 0; k < 10; ++k) c[k] = W.res[k][lane];
+        unwhiten_sums(Gq, ax, c, acc, n, W.g[lane]);
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Backward half of a run from its recorded hit list, in windows; the next
+// window's entries are loaded while the current one runs.
+__device__ inline void drain_hits(const SceneView &S, const Beam &B, HitWindow<kListWin> &W, const ReplayRay &mine,
+                                  const uint32_t *hg, const uint64_t *hm, int n_ent, uint64_t live, int lane,
+                                  float *acc) {
     uint32_t pg = 0;
     uint64_t pm = 0;
-    if (lane < min(kWin, n_ent)) {
+    if (lane < min(kListWin, n_ent)) {
         pg = hg[lane];
         pm = hm[lane] & live;
     }
-    for (int e0 = 0; e0 < n_ent; e0 += kWin) {
+    for (int e0 = 0; e0 < n_ent; e0 += kListWin) {
         const int64_t gj = pg;
         const uint64_t mj = pm;
-        const int e1 = e0 + kWin;
+        const int e1 = e0 + kListWin;
         pm = 0;
-        if (lane < min(kWin, n_ent - e1)) {
+        if (lane < min(kListWin, n_ent - e1)) {
             pg = hg[e1 + lane];
             pm = hm[e1 + lane] & live;
         }
-        const int cj = __builtin_popcountll(mj);
-        const int incl = wave_incl_scan(cj);
-        const int T = __builtin_amdgcn_readlane(incl, 63);
-        if (T == 0) continue;
-        // compact the entries with pairs into slots 0..nq-1
-        const uint64_t nonempty = ballot(cj > 0);
-        const int nq = __builtin_popcountll(nonempty);
-        if (cj > 0) {
-            const int q = __builtin_popcountll(nonempty & below);
-            W.rec[q] = S.rec[gj];
-            W.m[q] = mj;
-            W.g[q] = int32_t(gj);
-            W.incl[q] = incl;
-        }
-        if (lane < kWin)
-            for (int k = 0; k < 10; ++k) W.res[k][lane] = 0.0f;
-        __builtin_amdgcn_wave_barrier();
-        const int inclq = lane < nq ? W.incl[lane] : T;
-        // this lane's pairs: [p, p + left) of the window's T pairs
-        const int s = (T + 63) >> 6;
-        const int p = lane * s;
-        const int left = max(0, min(s, T - p));
-        // first slot whose inclusive count exceeds p (binary search over lanes)
-        int lo = 0, hi = kWin - 1;
-        for (int step = 0; step < kWinLog2; ++step) {
-            const int mid = (lo + hi) >> 1;
-            const int v = __shfl(inclq, mid, 64);
-            if (v > p) hi = mid; else lo = mid + 1;
-        }
-        int e = left > 0 ? lo : 0;
-        uint64_t m = W.m[e];
-        // skip the entry's first (p - exclusive prefix) rays
-        if (left > 0) m = drop_low_bits(m, p - (W.incl[e] - __builtin_popcountll(m)));
-        GaussRec G = W.rec[e];
-        float rho = G.rho_c * (1.0f / kSqrt2Pi);
-        float c[10];
-        for (int k = 0; k < 10; ++k) c[k] = 0.0f;
-        for (int it = 0; it < s; ++it) {
-            const bool act = it < left;
-            if (act && m == 0) {
-                // Entry e ends inside this lane's range, so no other lane
-                // leaves it inside the loop: the lanes that also hold part of
-                // it hold its start and add their sums after the loop. Its
-                // slot is still zero here, and a plain store replaces the
-                // LDS float atomic.
-                for (int k = 0; k < 10; ++k) {
-                    W.res[k][e] = c[k];
-                    c[k] = 0.0f;
-                }
-                e = min(e + 1, nq - 1);
-                m = W.m[e];
-                G = W.rec[e];
-                rho = G.rho_c * (1.0f / kSqrt2Pi);
-            }
-            // the gather runs on every lane (bpermute needs its sources active)
-            const int i = act ? __builtin_ctzll(m) : lane;
-            const RayRec Rr = gather_ray(mine, i);
-            if (act) {
-                m &= m - 1;
-                pair_grad(G.mu, G.P, rho, Rr, k2, c);
-            }
-        }
-        close_window<kWin>(W.part, W.res, c, left > 0 ? e : -1, lane);
-        if (lane < nq) {
-            const int64_t gq = W.g[lane];
-            for (int k = 0; k < 10; ++k) atomicAdd(&acc[k * n + gq], W.res[k][lane]);
-        }
-        __builtin_amdgcn_wave_barrier();
+        replay_window<kListWin>(B.rec, B.ax, S.n, W, gj, mj, mine, lane, acc);
     }
 }
 
@@ -595,144 +544,135 @@ __device__ inline float loss_weight(int kind, float I, float y, float b, double 
     return float(1.0 - double(y) / Ib);
 }
 
-// Gaussian-major backward of one packet by re-traversal: the candidates of
-// the traversal go into the per-wave LDS list; every 64 of them are one batch.
-// A Gaussian can be a candidate of several of the packet's runs, so a batch
-// ends with its run and takes that run's rays only.
-template <class Rays>
-__device__ inline void retraverse_backward(const LaunchTable &T, const SceneView &S, const Ray &R, TravLds &Lt,
-                                           const Rays &rays, uint64_t live_mask, int lane, float k2, float *acc) {
-    int count = 0;        // wave-uniform number of listed candidates
-    uint64_t listed = 0;  // the rays they are for
-    traverse_runs(T.traversal, S, R, live_mask, lane, Lt.stack, [&](int l, const RunRay &Q, const Beam &B) {
+// Backward of a run without a list (dL/dI given, or a list that outgrew its
+// region): the traversal takes the cutoff test of every candidate on the run's
+// weighted rays and collects the candidates that pass on any, one per lane;
+// every full window is replayed on the spot. A Gaussian per lane looping over all
+// rays, which it replaced, evaluated every candidate's gradient on every ray:
+// 50k Gaussians, 10 views of 256 x 256, 1116 -> 1074 us.
+__device__ inline void backward_by_windows(const LaunchTable &T, const SceneView &S, const Ray &R, const Beam &B,
+                                           const RunRay &Q, const ReplayRay &mine, bool live, TravLds &L, int lane,
+                                           float *acc) {
+    const float cut = live ? S.kappa2 : -1.0f;
+    int n = 0;  // pending entries (wave-uniform); lane q holds entry q
+    uint32_t pg = 0, plo = 0, phi = 0;
+    auto put = [&](int64_t g, uint64_t m) {
+        pg = uint32_t(lane_write(int(uint32_t(g)), n, int(pg)));
+        plo = uint32_t(lane_write(int(uint32_t(m)), n, int(plo)));
+        phi = uint32_t(lane_write(int(uint32_t(m >> 32)), n, int(phi)));
+        ++n;
+    };
+    auto replay = [&]() {
+        const uint64_t m = lane < n ? (uint64_t(phi) << 32) | plo : 0ull;
+        replay_window<kTravWin>(B.rec, B.ax, S.n, L.win, pg, m, mine, lane, acc);
+        n = 0;
+    };
+    traverse_run(T.traversal, S, R, B, live, lane, L.stack, [&](int l) {
         int64_t start;
-        const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-        if (!mask) return;
-        const uint64_t run = ballot(Q.cut >= 0.0f);
-        if (run != listed) {
-            if (count > 0) backward_batch(S, Lt, rays, count, listed, lane, k2, acc);
-            __builtin_amdgcn_wave_barrier();
-            count = 0;
-            listed = run;
-        }
-        if ((mask >> lane) & 1ull) {
-            const int pos = count + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
-            Lt.cand[pos] = int32_t(start + lane);
-        }
-        count += __builtin_popcountll(mask);
-        __builtin_amdgcn_wave_barrier();
-        if (count >= 64) {
-            backward_batch(S, Lt, rays, 64, listed, lane, k2, acc);
-            const int rest = count - 64;
-            int moved = 0;
-            if (lane < rest) moved = Lt.cand[64 + lane];
-            __builtin_amdgcn_wave_barrier();
-            if (lane < rest) Lt.cand[lane] = moved;
-            __builtin_amdgcn_wave_barrier();
-            count = rest;
+        uint64_t mask = leaf_candidates(S, B, l, lane, start);
+        while (mask) {
+            const int j0 = __builtin_ctzll(mask);
+            mask &= mask - 1;
+            const bool two = mask != 0;
+            const int j1 = two ? __builtin_ctzll(mask) : j0;
+            if (two) mask &= mask - 1;
+            const AxisRec G0 = sload(B.rec, start + j0);
+            const AxisRec G1 = sload(B.rec, start + j1);
+            hold_records(G0, G1);
+            AxisCore c;
+            float D, r;
+            axis_core(G0, Q, c);
+            pair_D(c, D, r);
+            const uint64_t h0 = ballot(D <= cut);
+            if (h0) put(start + j0, h0);
+            if (two) {
+                axis_core(G1, Q, c);
+                pair_D(c, D, r);
+                const uint64_t h1 = ballot(D <= cut);
+                if (h1) put(start + j1, h1);
+            }
+            if (n > kTravWin - 2) replay();
         }
     });
-    if (count > 0) backward_batch(S, Lt, rays, count, listed, lane, k2, acc);
+    if (n > 0) replay();
 }
 
+// One packet of the backward, run by run (each ray is in one run, so its
+// projection is complete when its run's traversal is).
 template <bool kFused>
-using WaveLdsOf = typename std::conditional<kFused, WaveLdsFused, WaveLdsPlain>::type;
-
-template <bool kFused>
-__device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int lane, WaveLdsOf<kFused> *L,
-                                       const BwdArgs &A, uint32_t *hit_g, uint64_t *hit_m) {
+__device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int lane, WaveLds *L, const BwdArgs &A,
+                                       uint32_t *hit_g, uint64_t *hit_m) {
     PacketRef P;
     if (!locate_packet(T, packet, lane, P)) return;
     const Segment &sg = T.segs[P.seg];
     const SceneView &S = T.scenes[sg.scene];
+    float *acc = kFused ? sg.acc : A.acc;
     Ray R;
     load_ray(sg.ro, sg.rd, sg.stride, P.ray, R);
-    const float k2 = S.kappa2;
-    if constexpr (kFused) {
-        float *acc = sg.acc;
-        bool listed = false;  // the forward half recorded a complete hit list
-        int n_ent = 0;
-        double sum = 0.0;
-        if (T.hit_cap > 0 && hit_g) {
-            HitList H{hit_g, hit_m, T.hit_cap, 0, 0, false, 0u, 0u, 0u};
-            traverse_runs(T.traversal, S, R, ballot(P.active), lane, L->t.stack, [&](int l, const RunRay &Q, const Beam &B) {
-                int64_t start;
-                const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-                leaf_forward_hits(B.rec, Q, start, mask, sum, H, lane);
-            });
-            H.flush(lane);
-            listed = !H.overflow;
-            n_ent = H.n;
-        } else {
-            uint32_t dummy = 0, dummy2 = 0;
-            traverse_runs(T.traversal, S, R, ballot(P.active), lane, L->t.stack, [&](int l, const RunRay &Q, const Beam &B) {
-                int64_t start;
-                const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-                leaf_forward<false>(B.rec, Q, start, mask, sum, dummy, dummy2);
-            });
-        }
-        const float I = float(sum);
-        double term = 0.0;
-        float w = 0.0f;
-        if (P.active) {
-            w = loss_weight(sg.loss_kind, I, sg.target[P.out], sg.background, term);
-            if (sg.out) sg.out[P.out] = I;
-        }
-        if (sg.loss) {
-            for (int off = 32; off >= 1; off >>= 1) term += __shfl_xor(term, off);
-            if (lane == 0) atomicAdd(sg.loss, term);
-        }
-        const bool live = P.active && w != 0.0f;
-        const uint64_t live_mask = ballot(live);
-        if (live_mask == 0) return;
-        // this lane's ray, handed to other lanes by bpermute / readlane
-        RayF mine;
-        for (int k = 0; k < 3; ++k) {
-            mine.o[k] = R.o[k];
-            mine.d[k] = R.d[k];
-        }
-        mine.w = live ? w : 0.0f;
-        if (listed) {
-            // the list's global stores (other lanes' entries) are visible to
-            // this wave's loads after a workgroup-scope release/acquire
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            drain_hits(S, L, mine, hit_g, hit_m, n_ent, live_mask, lane, k2, acc);
-            return;
-        }
-        retraverse_backward(T, S, R, L->t, RaysInLanes{mine}, live_mask, lane, k2, acc);
-    } else {
-        float *acc = A.acc;
-        const float w = P.active ? A.grad_out[P.out] : 0.0f;
-        const bool live = P.active && w != 0.0f;
-        const uint64_t live_mask = ballot(live);
-        if (live_mask == 0) return;
-        // stage the weighted rays, each at its lane's slot
-        if (live) {
-            RayRec &rr = L->rays[lane];
-            for (int k = 0; k < 3; ++k) {
-                rr.o[k] = R.o[k];
-                rr.d[k] = R.d[k];
+    float w = 0.0f;  // dL/dI
+    if (!kFused && P.active) w = A.grad_out[P.out];
+    double term = 0.0;
+    uint64_t todo = ballot(kFused ? P.active : P.active && w != 0.0f);
+    const Extent E = scene_extent(S);
+    while (todo) {
+        const uint64_t before = todo;
+        Beam B;
+        RunRay Q;
+        const uint64_t run = S.n > 0 ? next_run(E, R, todo, lane, B, Q) : (todo = 0);
+        const bool in = ((before & ~todo) >> lane) & 1ull;  // the run's rays, or one that is no line
+        Q.cut = in && run ? S.kappa2 : -1.0f;
+        B.rec = axis_rec_of(S, B.ax);
+        HitList H{hit_g, hit_m, T.hit_cap, 0, 0, !hit_g, 0u, 0u, 0u};
+        if (kFused) {
+            double sum = 0.0;
+            if (run)
+                traverse_run(T.traversal, S, R, B, in, lane, L->t.stack, [&](int l) {
+                    int64_t start;
+                    const uint64_t mask = leaf_candidates(S, B, l, lane, start);
+                    leaf_forward_hits(B.rec, Q, start, mask, sum, H, lane);
+                });
+            if (in) {
+                const float I = float(sum);
+                double t;
+                w = loss_weight(sg.loss_kind, I, sg.target[P.out], sg.background, t);
+                term += t;
+                if (sg.out) sg.out[P.out] = I;
             }
-            rr.w = w;
         }
-        __builtin_amdgcn_wave_barrier();
-        retraverse_backward(T, S, R, L->t, RaysInLds{L->rays}, live_mask, lane, k2, acc);
+        const bool live = in && w != 0.0f;
+        const uint64_t live_mask = ballot(live);
+        if (!run || !live_mask) continue;
+        const ReplayRay mine{Q.X1, Q.X2, Q.S1, Q.S2, live ? w / fabsf(float(Q.dk)) : 0.0f};
+        if (kFused) {
+            H.flush(lane);
+            if (!H.overflow) {
+                // the list's global stores (other lanes' entries) are visible to
+                // this wave's loads after a workgroup-scope release/acquire
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                drain_hits(S, B, L->win, mine, hit_g, hit_m, H.n, live_mask, lane, acc);
+                continue;
+            }
+        }
+        backward_by_windows(T, S, R, B, Q, mine, live, L->t, lane, acc);
+    }
+    if (kFused && sg.loss) {
+        for (int off = 32; off >= 1; off >>= 1) term += __shfl_xor(term, off);
+        if (lane == 0) atomicAdd(sg.loss, term);
     }
 }
 
-// 5 waves per SIMD (at most 96 VGPRs, against the 126 the fused form takes
-// unforced; a few registers spill): the forward half of the fused pass waits
-// on its records' loads, and the extra wave hides part of that latency
-// (persistent launches default to 20 waves per compute unit to match; LDS
-// holds 18 windows per compute unit, and later workgroups start as earlier
-// ones finish).
+// 5 waves per SIMD (at most 96 VGPRs; some spill, outside the pair loops): the
+// forward half of the fused pass waits on its records' loads, and the extra
+// wave hides part of that latency (persistent launches default to 20 waves per
+// compute unit to match; LDS holds 18 windows per compute unit, and later
+// workgroups start as earlier ones finish).
 template <bool kFused>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void k_backward(LaunchTable T, BwdArgs A) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-    WaveLdsOf<kFused> *L = reinterpret_cast<WaveLdsOf<kFused> *>(lds_raw) + wave;
+    WaveLds *L = reinterpret_cast<WaveLds *>(lds_raw + (kFused ? sizeof(WaveLds) : sizeof(TravLds)) * wave);
     const bool pull = T.work_counter != nullptr;
     // hit-list regions belong to persistent waves (one per wave slot)
     const int64_t slot = int64_t(blockIdx.x) * T.waves_per_group + wave;
@@ -874,9 +814,9 @@ static void launch_backward(LaunchTable &T, const BwdArgs &A, const LaunchShape 
     const unsigned groups = launch_groups(T, shape);
     const int waves = shape.waves;
     if (A.grad_out)
-        k_backward<false><<<dim3(groups), dim3(64 * waves), sizeof(WaveLdsPlain) * size_t(waves), st>>>(T, A);
+        k_backward<false><<<dim3(groups), dim3(64 * waves), sizeof(TravLds) * size_t(waves), st>>>(T, A);
     else
-        k_backward<true><<<dim3(groups), dim3(64 * waves), sizeof(WaveLdsFused) * size_t(waves), st>>>(T, A);
+        k_backward<true><<<dim3(groups), dim3(64 * waves), sizeof(WaveLds) * size_t(waves), st>>>(T, A);
 }
 
 hipError_t enqueue_backward(LaunchTable &T, const BwdArgs &A, const gr_scene &sc, const uint32_t *order,
