@@ -136,7 +136,9 @@ gr_status gr_scene_status(const gr_scene *scene, int32_t *flags /* host */, void
 /* ------------------------------------------------------------------------ */
 
 /* Optional tuning knobs (NULL = defaults). A field set to 0 takes its default.
- * waves_per_group: waves (of 64 rays each) per workgroup, 1..16 (default 1).
+ * waves_per_group: waves (of 64 rays each) per workgroup, 1..16 (default 1;
+ *   with the default, launches of few packets run a packet on up to 16 waves of
+ *   a workgroup, each with a part of the scene).
  * xcd_remap: 1 (default) maps consecutive ray packets to the same XCD, 2
  *   disables the remap (grid launches only).
  * traversal: 2 (default) walks the 64-wide hierarchy over the Morton-ordered
@@ -147,7 +149,7 @@ gr_status gr_scene_status(const gr_scene *scene, int32_t *flags /* host */, void
  *   persistent_groups workgroups (0 = 20 waves per compute unit) loop, each
  *   wave taking the next packet from the counter with an atomic; the library
  *   zeroes the counter on the stream first. Concurrent calls need distinct
- *   counters. Results are identical to the grid launch.
+ *   counters. Same results.
  * hit_list_cap: hit-list entries per wave for the fused-loss backward (see
  *   gr_fused_scratch_bytes): 0 = default (8192), -1 = never record hit lists,
  *   else 64..1048576.
@@ -182,7 +184,10 @@ typedef struct gr_launch {
  * the integral over the parameter t, so it scales as 1/|d|); d = 0 is invalid
  * and yields NaN or 0. Rays are processed in packets of 64 consecutive rays;
  * coherent packets (as written by the ray generators below) run fastest.
- * Summation order inside a ray is fixed, so the result is deterministic. */
+ * Summation order inside a ray is fixed for a given launch (number of rays and
+ * options), so the result is deterministic; launches that split packets differ
+ * from others in the order of a ray's FP64 sum, which shows in the FP32 result's
+ * last bit in about one ray of 10^8. "Same results" below is up to that. */
 gr_status gr_project(const gr_scene *scene, const float *ray_o, const float *ray_d, int64_t n_rays,
                      float *out, const gr_launch *opt, void *stream);
 
@@ -207,8 +212,8 @@ gr_status gr_project_stats(const gr_scene *scene, const float *ray_o, const floa
  * its own SoA ray arrays ray_o[3 stride], ray_d[3 stride] (stride = the
  * length of each component block); it projects rays
  * [ray_offset, ray_offset + n_rays) into out[out_offset ...]. Each segment's
- * 64-ray packets start at its ray_offset, so its results equal gr_project on
- * those rays alone, bit for bit. The segment table is passed to the kernel by
+ * 64-ray packets start at its ray_offset, so its results are the same as
+ * gr_project's on those rays alone. The segment table is passed to the kernel by
  * value: at most GR_MAX_SEGMENTS segments and GR_MAX_SCENES scenes. */
 #define GR_MAX_SEGMENTS 32
 #define GR_MAX_SCENES 8

@@ -74,6 +74,8 @@ gr_status check_launch(const gr_launch *opt, LaunchShape &sh) {
     sh.work_counter = nullptr;
     sh.hit_cap = kDefaultHitCap;
     sh.precision = 0;
+    sh.free_waves = !opt || opt->waves_per_group <= 1;
+    sh.free_groups = sh.free_waves && (!opt || (!opt->persistent_groups && !opt->work_counter));
     if (!opt) return GR_OK;
     if (opt->precision != 0 && opt->precision != 1) return GR_E_ARG;
     sh.precision = opt->precision;

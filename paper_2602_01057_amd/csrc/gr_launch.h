@@ -1,6 +1,8 @@
 // Launch tables shared by the projection kernels and the C ABI layer.
 #pragma once
 
+#include <math.h>
+
 #include "gr_internal.h"
 
 namespace gr {
@@ -39,6 +41,7 @@ struct LaunchTable {
     uint32_t *work_counter;  // non-NULL: persistent launch
     int32_t traversal;       // 1 binary LBVH, 2 wide hierarchy
     int32_t precision;       // forward: 0 FP64 quadratic forms, 1 compact FP32 records
+    int32_t parts;           // parts a packet's leaves are dealt out to (packet_parts)
     int32_t hit_cap;         // > 0: fused backward records hit lists (persistent only)
     uint32_t *hit_g;         // per-wave-slot regions of hit_cap entries each
     uint64_t *hit_m;
@@ -64,7 +67,39 @@ struct LaunchShape {
     uint32_t *work_counter;
     int hit_cap;  // hit-list entries per wave for the fused backward (0 = re-traverse)
     int precision;  // forward only: 0 FP64 (default), 1 compact FP32 records
+    bool free_waves;  // the caller left waves per group to the library
+    bool free_groups; // and the persistent launch's shape
 };
+
+// Parts of a packet. A packet is a serial chain of record loads and pair
+// evaluations on one wave, so a launch of few packets waits for the longest
+// chain with the chip nearly empty: its leaves are dealt out in turn (leaf j of
+// the packet to part j mod parts) to several waves. Each part repeats the beam
+// and the upper levels, which only pays while the chip has room and the chain
+// is long; the longer the larger the scene. Measured best number of parts
+// (forward, us, parts 1 / 2 / 4 / 8):
+//   512 Gaussians, 512 packets 21 / 20 / 19 / 19, 2048 packets 23 / 24 / 24 / 33;
+//   5,000, 2048 packets 101 / 73 / 56 / 60, 8192 packets 168 / 134 / 138 / 193;
+//   50,000, 2048 packets 804 / 473 / 302 / 229, 8192 packets 1050 / 713 / 653 / 728;
+//   500,000, 8192 packets 7639 / 4923 / 4054 / 4036;
+// which waves = parts x packets near kPartWaves sqrt(leaves) follows, and the
+// backward with it. More than 65,536 waves only repeat beams (16 views of
+// 512 x 512 on the 500k scene: 7.8 ms whole, 8.8 ms halved), and 16 parts, a
+// workgroup that leaves a compute unit no room for a second, are for the few
+// packets of coarse views of large scenes (64 packets on the 500k scene:
+// 12.4 ms whole, 2.0 ms in 8 parts, 1.2 ms in 16; 2048 packets 14.5, 3.4, 3.8).
+constexpr double kPartWaves = 2048.0;
+constexpr int kMaxParts = 16;
+inline int packet_parts(int64_t packets, int32_t n_leaves) {
+    const double room = kPartWaves * sqrt(double(n_leaves));
+    int parts = kMaxParts;
+    while (parts > 1) {
+        const double most = parts == 16 ? 8192.0 : parts == 2 ? 32768.0 : 65536.0;
+        if (parts <= n_leaves && double(packets) * parts <= (room < most ? room : most)) break;
+        parts /= 2;
+    }
+    return parts;
+}
 
 hipError_t enqueue_forward(LaunchTable &T, const LaunchShape &shape, hipStream_t st,
                            uint64_t *stats = nullptr);
@@ -88,6 +123,10 @@ inline void finish_table(LaunchTable &T, const LaunchShape &shape) {
         pk += (T.segs[s].n_rays + 63) / 64;
     }
     T.n_packets = pk;
+    int32_t leaves = 1;
+    for (int s = 0; s < T.n_segs; ++s)
+        if (T.scenes[T.segs[s].scene].n_leaves > leaves) leaves = T.scenes[T.segs[s].scene].n_leaves;
+    T.parts = packet_parts(pk, leaves);
     T.waves_per_group = shape.waves;
     T.xcd_remap = shape.remap;
     T.persistent_groups = shape.persistent_groups;
@@ -96,10 +135,10 @@ inline void finish_table(LaunchTable &T, const LaunchShape &shape) {
     T.precision = shape.precision;
 }
 
-// Workgroups of a launch: one wave per packet, or the persistent count.
-inline unsigned launch_groups(const LaunchTable &T, const LaunchShape &shape) {
+// Workgroups of a launch: one wave per work item, or the persistent count.
+inline unsigned launch_groups(int64_t items, const LaunchShape &shape) {
     if (shape.work_counter) return unsigned(shape.persistent_groups);
-    return unsigned((T.n_packets + shape.waves - 1) / shape.waves);
+    return unsigned((items + shape.waves - 1) / shape.waves);
 }
 
 // Zero-fill kernels (capturable in a graph, unlike a memset node).

@@ -37,6 +37,8 @@
 // half and replays it with the pairs spread evenly over the lanes; with dL/dI
 // given, or for a list that outgrew its region, the traversal runs again with
 // the cutoff test alone and its hits are replayed window by window.
+#include <algorithm>
+
 #include "gr_trace.h"
 
 namespace gr {
@@ -149,10 +151,11 @@ __device__ inline void leaf_forward32(const SceneView &S, const Ray &R, float in
 
 // One packet of the forward pass. kStats adds work counters (atomics once per
 // packet) for measurement runs; the production instantiation has none.
-// kCompact selects the FP32 precision mode.
-template <bool kStats, bool kCompact>
-__device__ inline void packet_forward(const LaunchTable &T, int64_t packet, int lane, uint32_t *stack,
-                                      uint64_t *stats) {
+// kCompact selects the FP32 precision mode. With kTeam the workgroup's waves
+// take one part each and meet in `sums` (64 per wave).
+template <bool kStats, bool kCompact, bool kTeam>
+__device__ inline void packet_forward(const LaunchTable &T, int64_t packet, int lane, int wave, uint32_t *stack,
+                                      double *sums, uint64_t *stats) {
     PacketRef P;
     if (!locate_packet(T, packet, lane, P)) return;
     const Segment &sg = T.segs[P.seg];
@@ -160,22 +163,31 @@ __device__ inline void packet_forward(const LaunchTable &T, int64_t packet, int 
     float *out = sg.out;
     Ray R;
     load_ray(sg.ro, sg.rd, sg.stride, P.ray, R);
-    double acc = 0.0;
+    double total = 0.0;
     uint32_t n_inc = 0, n_cand = 0, n_leaf = 0, n_hitc = 0;
     const float inv_dd = kCompact ? 1.0f / (R.d[0] * R.d[0] + R.d[1] * R.d[1] + R.d[2] * R.d[2]) : 0.0f;
-    traverse_runs(T.traversal, S, R, ballot(P.active), lane, stack, [&](int l, const RunRay &Q, const Beam &B) {
-        int64_t start;
-        const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-        if (kStats) {
-            ++n_leaf;
-            n_cand += __builtin_popcountll(mask);
-        }
-        if constexpr (kCompact)
-            leaf_forward32<kStats>(S, R, inv_dd, start, mask, Q.cut, acc, n_inc, n_hitc);
-        else
-            leaf_forward<kStats>(B.rec, Q, start, mask, acc, n_inc, n_hitc);
+    const Part part = kTeam ? Part{T.parts - 1, wave} : Part{0, 0};
+    for_runs(S, R, ballot(P.active), lane, [&](bool in, const RunRay &Q, const Beam &B) {
+        traverse_run(T.traversal, S, R, B, in, lane, stack, part, [&](int l) {
+            int64_t start;
+            const uint64_t mask = leaf_candidates(S, B, l, lane, start);
+            if (kStats) {
+                ++n_leaf;
+                n_cand += __builtin_popcountll(mask);
+            }
+            if constexpr (kCompact)
+                leaf_forward32<kStats>(S, R, inv_dd, start, mask, Q.cut, total, n_inc, n_hitc);
+            else
+                leaf_forward<kStats>(B.rec, Q, start, mask, total, n_inc, n_hitc);
+        });
     });
-    if (P.active) out[P.out] = float(acc);
+    if (kTeam) {
+        sums[wave * 64 + lane] = total;
+        __syncthreads();
+        if (wave != 0) return;
+        for (int k = 1; k < T.parts; ++k) total += sums[k * 64 + lane];
+    }
+    if (P.active) out[P.out] = float(total);
     if (kStats) {
         const float inc = wave_sum(float(n_inc));
         const uint64_t act = ballot(P.active);
@@ -206,9 +218,21 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     const bool pull = T.work_counter != nullptr;
     int64_t packet = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
     while (packet < T.n_packets) {
-        packet_forward<kStats, kCompact>(T, packet, lane, stack, stats);
+        packet_forward<kStats, kCompact, false>(T, packet, lane, 0, stack, nullptr, stats);
         packet = pull ? next_packet(T.work_counter, lane) : T.n_packets;
     }
+}
+
+// The forward of a launch of few packets: one workgroup per packet, one wave
+// per part.
+template <bool kCompact>
+__global__ __launch_bounds__(1024) void k_forward_team(LaunchTable T) {
+    extern __shared__ __align__(16) unsigned char team_lds[];  // 64 sums, then kWideStack entries per wave
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    double *sums = reinterpret_cast<double *>(team_lds);
+    uint32_t *stack = reinterpret_cast<uint32_t *>(sums + 64 * T.waves_per_group) + wave * kWideStack;
+    packet_forward<false, kCompact, true>(T, logical_block(T.xcd_remap), lane, wave, stack, sums, nullptr);
 }
 
 // A ray as its lane holds it for the replay of its run: the line across the
@@ -552,7 +576,7 @@ __device__ inline float loss_weight(int kind, float I, float y, float b, double 
 // 50k Gaussians, 10 views of 256 x 256, 1116 -> 1074 us.
 __device__ inline void backward_by_windows(const LaunchTable &T, const SceneView &S, const Ray &R, const Beam &B,
                                            const RunRay &Q, const ReplayRay &mine, bool live, TravLds &L, int lane,
-                                           float *acc) {
+                                           Part part, float *acc) {
     const float cut = live ? S.kappa2 : -1.0f;
     int n = 0;  // pending entries (wave-uniform); lane q holds entry q
     uint32_t pg = 0, plo = 0, phi = 0;
@@ -567,7 +591,7 @@ __device__ inline void backward_by_windows(const LaunchTable &T, const SceneView
         replay_window<kTravWin>(B.rec, B.ax, S.n, L.win, pg, m, mine, lane, acc);
         n = 0;
     };
-    traverse_run(T.traversal, S, R, B, live, lane, L.stack, [&](int l) {
+    traverse_run(T.traversal, S, R, B, live, lane, L.stack, part, [&](int l) {
         int64_t start;
         uint64_t mask = leaf_candidates(S, B, l, lane, start);
         while (mask) {
@@ -598,15 +622,21 @@ __device__ inline void backward_by_windows(const LaunchTable &T, const SceneView
 }
 
 // One packet of the backward, run by run (each ray is in one run, so its
-// projection is complete when its run's traversal is).
-template <bool kFused>
-__device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int lane, WaveLds *L, const BwdArgs &A,
-                                       uint32_t *hit_g, uint64_t *hit_m) {
+// projection is complete when its run's traversal is). With kTeam the
+// workgroup's waves take a part of the leaves each, meet in `sums` (64 per
+// wave) for the projection, and replay the lists of their own parts. With dL/dI
+// given the packet's parts are work items of their own.
+template <bool kFused, bool kTeam>
+__device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int lane, int part, WaveLds *L,
+                                       double *sums, const BwdArgs &A, uint32_t *hit_g, uint64_t *hit_m) {
     PacketRef P;
     if (!locate_packet(T, packet, lane, P)) return;
     const Segment &sg = T.segs[P.seg];
     const SceneView &S = T.scenes[sg.scene];
     float *acc = kFused ? sg.acc : A.acc;
+    const int parts = kFused && !kTeam ? 1 : T.parts;
+    const Part mine_only{parts - 1, part};
+    const bool first = !kTeam || part == 0;
     Ray R;
     load_ray(sg.ro, sg.rd, sg.stride, P.ray, R);
     float w = 0.0f;  // dL/dI
@@ -624,19 +654,27 @@ __device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int
         B.rec = axis_rec_of(S, B.ax);
         HitList H{hit_g, hit_m, T.hit_cap, 0, 0, !hit_g, 0u, 0u, 0u};
         if (kFused) {
-            double sum = 0.0;
+            double total = 0.0;
             if (run)
-                traverse_run(T.traversal, S, R, B, in, lane, L->t.stack, [&](int l) {
+                traverse_run(T.traversal, S, R, B, in, lane, L->t.stack, mine_only, [&](int l) {
                     int64_t start;
                     const uint64_t mask = leaf_candidates(S, B, l, lane, start);
-                    leaf_forward_hits(B.rec, Q, start, mask, sum, H, lane);
+                    leaf_forward_hits(B.rec, Q, start, mask, total, H, lane);
                 });
+            if (kTeam) {
+                // (all waves of the workgroup take the same runs)
+                __syncthreads();  // the last run's sums are read
+                sums[part * 64 + lane] = total;
+                __syncthreads();
+                total = sums[lane];
+                for (int p = 1; p < parts; ++p) total += sums[p * 64 + lane];
+            }
             if (in) {
-                const float I = float(sum);
+                const float I = float(total);
                 double t;
                 w = loss_weight(sg.loss_kind, I, sg.target[P.out], sg.background, t);
                 term += t;
-                if (sg.out) sg.out[P.out] = I;
+                if (first && sg.out) sg.out[P.out] = I;
             }
         }
         const bool live = in && w != 0.0f;
@@ -654,9 +692,9 @@ __device__ inline void packet_backward(const LaunchTable &T, int64_t packet, int
                 continue;
             }
         }
-        backward_by_windows(T, S, R, B, Q, mine, live, L->t, lane, acc);
+        backward_by_windows(T, S, R, B, Q, mine, live, L->t, lane, mine_only, acc);
     }
-    if (kFused && sg.loss) {
+    if (kFused && first && sg.loss) {
         for (int off = 32; off >= 1; off >>= 1) term += __shfl_xor(term, off);
         if (lane == 0) atomicAdd(sg.loss, term);
     }
@@ -679,10 +717,36 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void 
     const bool lists = pull && T.hit_cap > 0;
     uint32_t *hg = lists ? T.hit_g + slot * T.hit_cap : nullptr;
     uint64_t *hm = lists ? T.hit_m + slot * T.hit_cap : nullptr;
-    int64_t packet = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
-    while (packet < T.n_packets) {
-        packet_backward<kFused>(T, packet, lane, L, A, hg, hm);
-        packet = pull ? next_packet(T.work_counter, lane) : T.n_packets;
+    // with dL/dI given, a packet's parts are work items of their own
+    const int parts = kFused ? 1 : T.parts;
+    const int64_t n_items = T.n_packets * parts;
+    int64_t item = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
+    while (item < n_items) {
+        const int64_t packet = kFused ? item : item / parts;
+        packet_backward<kFused, false>(T, packet, lane, int(item - packet * parts), L, nullptr, A, hg, hm);
+        item = pull ? next_packet(T.work_counter, lane) : n_items;
+    }
+}
+
+// The fused pass of a launch of few packets: workgroups take packets, their
+// waves one part each (with hit lists, so always persistent).
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_backward_team(LaunchTable T) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    WaveLds *L = reinterpret_cast<WaveLds *>(lds_raw) + wave;
+    double *sums = reinterpret_cast<double *>(lds_raw + sizeof(WaveLds) * T.waves_per_group);
+    uint32_t *ticket = reinterpret_cast<uint32_t *>(sums + 64 * T.waves_per_group);
+    const int64_t slot = int64_t(blockIdx.x) * T.waves_per_group + wave;
+    const BwdArgs none{nullptr, nullptr};
+    for (;;) {
+        if (threadIdx.x == 0) *ticket = atomicAdd(T.work_counter, 1u);
+        __syncthreads();
+        const int64_t packet = int64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(*ticket))));
+        if (packet >= T.n_packets) return;
+        packet_backward<true, true>(T, packet, lane, wave, L, sums, none, T.hit_g + slot * T.hit_cap,
+                                    T.hit_m + slot * T.hit_cap);
+        __syncthreads();  // the ticket and the sums are read
     }
 }
 
@@ -785,7 +849,17 @@ hipError_t enqueue_forward(LaunchTable &T, const LaunchShape &shape, hipStream_t
     finish_table(T, shape);
     if (T.n_packets == 0) return hipSuccess;
     if (shape.work_counter) k_zero_u32<<<1, 64, 0, st>>>(shape.work_counter);
-    const unsigned groups = launch_groups(T, shape);
+    const int team = T.parts;
+    if (team > 1 && shape.free_waves && !shape.work_counter && !stats) {
+        T.waves_per_group = team;
+        const size_t lds = (sizeof(double) * 64 + sizeof(uint32_t) * kWideStack) * size_t(team);
+        if (T.precision == 1)
+            k_forward_team<true><<<dim3(unsigned(T.n_packets)), dim3(64 * team), lds, st>>>(T);
+        else
+            k_forward_team<false><<<dim3(unsigned(T.n_packets)), dim3(64 * team), lds, st>>>(T);
+        return hipGetLastError();
+    }
+    const unsigned groups = launch_groups(T.n_packets, shape);
     const int waves = shape.waves;
     const size_t lds = T.traversal == 1 ? 0 : sizeof(uint32_t) * kWideStack * size_t(waves);
     if (T.precision == 1) {
@@ -811,7 +885,16 @@ static void launch_backward(LaunchTable &T, const BwdArgs &A, const LaunchShape 
     T.hit_m = lists ? hit_m : nullptr;
     if (T.n_packets == 0) return;
     if (shape.work_counter) k_zero_u32<<<1, 64, 0, st>>>(shape.work_counter);
-    const unsigned groups = launch_groups(T, shape);
+    const int team = T.parts;
+    if (team > 1 && lists && shape.free_groups) {
+        // as many waves as the lists' regions were sized for
+        T.waves_per_group = team;
+        const unsigned groups = unsigned(std::min<int64_t>(T.n_packets, shape.persistent_groups / team));
+        const size_t lds = (sizeof(WaveLds) + sizeof(double) * 64) * size_t(team) + 16;
+        k_backward_team<<<dim3(groups), dim3(64 * team), lds, st>>>(T);
+        return;
+    }
+    const unsigned groups = launch_groups(A.grad_out ? T.n_packets * T.parts : T.n_packets, shape);
     const int waves = shape.waves;
     if (A.grad_out)
         k_backward<false><<<dim3(groups), dim3(64 * waves), sizeof(TravLds) * size_t(waves), st>>>(T, A);

@@ -403,7 +403,7 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
             }
         }
     };
-    traverse_run(T.traversal, S, R, B, in, lane, stack, [&](int l) {
+    traverse_run(T.traversal, S, R, B, in, lane, stack, Part{0, 0}, [&](int l) {
         int64_t start;
         uint64_t mask = leaf_candidates(S, B, l, lane, start);
         // two candidates per step (their records load together)
@@ -608,7 +608,7 @@ __device__ inline void replay_backward(const SceneView &S, const TofWave<TofWinB
 }
 
 template <int kBins>
-__device__ inline void packet_backward_tof(const LaunchTable &T, const TofArgs &A, int64_t packet, int lane,
+__device__ inline void packet_backward_tof(const LaunchTable &T, const TofArgs &A, int64_t packet, int part, int lane,
                                            const TofWave<TofWinB> &L) {
     PacketRef P;
     if (!locate_packet(T, packet, lane, P)) return;
@@ -640,11 +640,12 @@ __device__ inline void packet_backward_tof(const LaunchTable &T, const TofArgs &
     mine.c = ray_center(A, P.ray);
     float *acc = A.acc;
     TofPending pe{0, 0u, 0ull};
-    traverse_runs(T.traversal, S, R, ballot(live), lane, L.stack, [&](int l, const RunRay &V, const Beam &B) {
+    for_runs(S, R, ballot(live), lane, [&](bool in, const RunRay &V, const Beam &B) {
+    const float k2r = V.cut;
+    const AxisRec *rec = B.rec;
+    traverse_run(T.traversal, S, R, B, in, lane, L.stack, Part{T.parts - 1, part}, [&](int l) {
         int64_t start;
         uint64_t mask = leaf_candidates(S, B, l, lane, start);
-        const float k2r = V.cut;
-        const AxisRec *rec = B.rec;
         while (mask) {
             const int j0 = __builtin_ctzll(mask);
             mask &= mask - 1;
@@ -672,6 +673,7 @@ __device__ inline void packet_backward_tof(const LaunchTable &T, const TofArgs &
             }
         }
     });
+    });
     if (pe.n > 0) replay_backward<kBins>(S, L, pe, mine, lane, k2, tb, acc);
 }
 
@@ -682,10 +684,12 @@ __global__ __launch_bounds__(256) void k_backward_tof(LaunchTable T, TofArgs A) 
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const TofWave<TofWinB> L = tof_wave<TofWinB>(tof_lds, wave, tof_rows(A.n_bins > 0 ? A.n_bins : 1));
     const bool pull = T.work_counter != nullptr;
-    int64_t packet = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
-    while (packet < T.n_packets) {
-        packet_backward_tof<kBins>(T, A, packet, lane, L);
-        packet = pull ? next_packet(T.work_counter, lane) : T.n_packets;
+    // a packet's parts are work items of their own
+    const int64_t n_items = T.n_packets * T.parts;
+    int64_t item = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
+    while (item < n_items) {
+        packet_backward_tof<kBins>(T, A, item / T.parts, int(item % T.parts), lane, L);
+        item = pull ? next_packet(T.work_counter, lane) : n_items;
     }
 }
 
@@ -741,7 +745,7 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_weights(int32_t kind, con
 
 template <int kBins>
 hipError_t launch_forward(LaunchTable &T, const TofArgs &A, const LaunchShape &shape, hipStream_t st) {
-    const unsigned groups = launch_groups(T, shape);
+    const unsigned groups = launch_groups(T.n_packets, shape);
     const size_t lds = (sizeof(TofQueue) + sizeof(uint32_t) * kWideStack) * size_t(shape.waves);
     k_forward_tof<kBins><<<dim3(groups), dim3(64 * shape.waves), lds, st>>>(T, A);
     return hipGetLastError();
@@ -749,7 +753,7 @@ hipError_t launch_forward(LaunchTable &T, const TofArgs &A, const LaunchShape &s
 
 template <int kBins>
 hipError_t launch_backward(LaunchTable &T, const TofArgs &A, const LaunchShape &shape, hipStream_t st) {
-    const unsigned groups = launch_groups(T, shape);
+    const unsigned groups = launch_groups(T.n_packets * T.parts, shape);
     const size_t lds = tof_wave_bytes<TofWinB>(tof_rows(A.n_bins > 0 ? A.n_bins : 1)) * size_t(shape.waves);
     k_backward_tof<kBins><<<dim3(groups), dim3(64 * shape.waves), lds, st>>>(T, A);
     return hipGetLastError();

@@ -665,23 +665,32 @@ __device__ inline void traverse_wide(const SceneView &S, const Beam &B, int lane
     if (err && lane == 0) atomicOr(const_cast<int32_t *>(&S.hdr->flags), err);
 }
 
+// The leaves of a traversal that part `part` of `parts` (a power of 2) takes:
+// every parts-th, in the order they come.
+struct Part {
+    int mask, part;
+};
+
 // Walks the scene for one run: mode 2 = wide hierarchy (default), 1 = binary
 // LBVH with slab tests of the run's rays (`in`).
 template <class LeafFn>
 __device__ inline void traverse_run(int mode, const SceneView &S, const Ray &R, const Beam &B, bool in, int lane,
-                                    uint32_t *stack, LeafFn &&leaf_fn) {
+                                    uint32_t *stack, Part part, LeafFn &&leaf_fn) {
+    int ord = 0;
+    auto leaf = [&](int l) {
+        if ((ord++ & part.mask) == part.part) leaf_fn(l);
+    };
     if (mode == 1)
-        traverse(S, R, in, lane, leaf_fn);
+        traverse(S, R, in, lane, leaf);
     else
-        traverse_wide(S, B, lane, stack, leaf_fn);
+        traverse_wide(S, B, lane, stack, leaf);
 }
 
-// Walks the scene for the rays of `todo`, run by run: f(l, Q, B) is called for
-// every leaf l a run may meet, in Morton order, with Q the lane's ray (whose
-// cut lets no lane outside the run count).
-template <class LeafFn>
-__device__ inline void traverse_runs(int mode, const SceneView &S, const Ray &R, uint64_t todo, int lane,
-                                     uint32_t *stack, LeafFn &&leaf_fn) {
+// Takes the rays of `todo` run by run: f(in, Q, B) is called for each run, with
+// `in` true on its lanes and Q the lane's ray (whose cut lets no lane outside
+// the run count).
+template <class RunFn>
+__device__ inline void for_runs(const SceneView &S, const Ray &R, uint64_t todo, int lane, RunFn &&run_fn) {
     if (S.n == 0) return;
     const Extent E = scene_extent(S);
     while (todo) {
@@ -692,7 +701,7 @@ __device__ inline void traverse_runs(int mode, const SceneView &S, const Ray &R,
         const bool in = (run >> lane) & 1ull;
         Q.cut = in ? S.kappa2 : -1.0f;
         B.rec = axis_rec_of(S, B.ax);
-        traverse_run(mode, S, R, B, in, lane, stack, [&](int l) { leaf_fn(l, Q, B); });
+        run_fn(in, Q, B);
     }
 }
 

@@ -1,0 +1,70 @@
+"""Launches of few packets, where a packet's leaves are dealt out to the waves
+of a workgroup: against the FP64 oracle, and against the launches that run a
+packet on one wave (the per-ray FP64 sum is taken in another order there, so an
+FP32 result may differ in its last bit)."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import geometry as G
+from paper_2602_01057_amd.inputs import sample_scene, sample_unit_weights
+from parity import assert_forward, assert_grad, gpu_grad_rows
+
+pytestmark = pytest.mark.gpu
+
+LAST_BIT = 1.2e-7
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+# (Gaussians, leaf size, views, nu, nv): one leaf (no parts), as many leaves as parts and one more or less,
+# one ragged packet, packets of several runs, and more packets than workgroups take at once
+@pytest.mark.parametrize("n,leaf,views,nu,nv", [(50, 64, 1, 8, 8), (130, 64, 1, 5, 7), (15 * 16, 16, 2, 8, 8),
+                                                (17 * 16 - 3, 16, 3, 19, 11), (400, 1, 2, 16, 8),
+                                                (1500, 8, 5, 33, 21), (900, 64, 40, 40, 24)])
+def test_parts_against_oracle_and_whole_packets(gr, n, leaf, views, nu, nv):
+    import torch
+    sc = sample_scene(n, seed=31 + n, radius=60.0, scale_range=(1.0, 9.0))
+    g = dict(kind="ct", cone=1, n_views=views, nu=nu, nv=nv, angle0=0.1, angle_range=5.0, dso=400.0, dsd=700.0,
+             pitch_u=190.0 / nu, pitch_v=190.0 / nv, offset_u=0.0, offset_v=0.0, tile_u=8, tile_v=8)
+    o, d = G.rays32(g)
+    m = o.shape[1]
+    S = gr.Scene(*[_dev(a) for a in (sc.mean, sc.scale, sc.quat, sc.density)], leaf_size=leaf)
+    ro, rd = _dev(o), _dev(d)
+    ref = oracle.project(sc, o, d)
+    near = lambda a, b: torch.allclose(a, b, rtol=LAST_BIT, atol=0.0)  # noqa: E731
+    I = gr.project(S, ro, rd)
+    assert_forward(I.cpu().numpy(), ref, what="parts")
+    for kw in (dict(waves_per_group=2), dict(persistent=True), dict(traversal=1), dict(traversal=1, persistent=3)):
+        assert near(gr.project(S, ro, rd, **kw), I), kw
+    assert near(gr.project_stats(S, ro, rd)[0], I)
+    assert near(gr.project(S, ro, rd, precision="fp32"), gr.project(S, ro, rd, precision="fp32", waves_per_group=2))
+    out = torch.full((m,), -1.0, device="cuda")
+    cut = min(m, 64 * (1 + m // 200))
+    gr.project_batched([S], [(0, ro, rd, 0, cut, out, 0), (0, ro, rd, cut, m - cut, out, cut)])
+    assert near(out, I)
+    rng = np.random.default_rng(6)
+    off = rng.uniform(0.5, 1.5, m) * rng.choice([-1.0, 1.0], m)
+    y = (ref["I_kappa"] + off * max(1e-3, float(ref["I_kappa"].mean()))).astype(np.float32)
+    # (weights of the projection checked above: a pair on the cutoff, where either decision is right, moves its
+    # ray's weight and with it every Gaussian on the ray)
+    L, w = oracle.loss_weights("l2", I.cpu().numpy().astype(np.float64), y.astype(np.float64))
+    want = oracle.grad(sc, o, d, w)
+    idx = np.arange(n)
+    for kw in (dict(), dict(hit_list_cap=64), dict(hit_list_cap=-1), dict(traversal=1), dict(persistent=2)):
+        proj, loss = torch.empty(m, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+        got = gr.project_backward(S, ro, rd, loss="l2", target=_dev(y), out_proj=proj, out_loss=loss, **kw)
+        assert near(proj, I), kw
+        assert abs(loss.item() - L) <= 1e-4 * L, kw
+        assert_grad(gpu_grad_rows(got, idx), want, what=f"fused {kw}")
+    w = sample_unit_weights(m, 3)
+    want = oracle.grad(sc, o, d, w.astype(np.float64))
+    for kw in (dict(), dict(waves_per_group=4), dict(persistent=2), dict(traversal=1)):
+        assert_grad(gpu_grad_rows(gr.project_backward(S, ro, rd, _dev(w), **kw), idx), want, what=f"backward {kw}")
+    want = oracle.grad_tof(sc, o, d, np.stack([w, -w, 0.5 * w]).astype(np.float64), 3, 40.0, 60.0)
+    got = gr.project_tof_backward(S, ro, rd, _dev(np.stack([w, -w, np.float32(0.5) * w])), 3, sigma=40.0, bin_width=60.0)
+    assert_grad(gpu_grad_rows(got, idx), want, what="tof backward")
+    assert S.status_flags() == 0
