@@ -48,11 +48,14 @@ namespace gr {
 // ---------------------------------------------------------------------------
 
 // Forward sum over one leaf's candidate Gaussians (mask), two records per
-// step. The compiler issues each record's scalar loads at its first use (the
-// density's inside the branch of the lanes within the cutoff); the 8 waves per
-// SIMD of k_forward hide those latencies. Holding both records before the
-// first evaluation (hold_records, as the recording loop of the fused pass
-// does) ran this kernel 4% slower: more scalar registers spill at 8 waves.
+// step. The compiler issues each record's scalar loads at its first use; the 8
+// waves per SIMD of k_forward hide that latency. The density is taken with the
+// record (load_whole): inside the branch of the lanes within the cutoff, where
+// the compiler would put it, it is a second wait per pair (50k Gaussians, 50
+// views of 256 x 256: 1819 -> 1781 us, one small view 14.3 -> 13.7 us, the 500k
+// scene the same). Holding both records before the first evaluation
+// (hold_records, as the recording loop of the fused pass does) is slower here:
+// 1873 us, more scalar registers spill at 8 waves.
 template <bool kStats>
 __device__ inline void leaf_forward(const AxisRec *rec, const RunRay &Q, int64_t start, uint64_t mask,
                                     double &acc, uint32_t &n_inc, uint32_t &n_hitc) {
@@ -67,6 +70,7 @@ __device__ inline void leaf_forward(const AxisRec *rec, const RunRay &Q, int64_t
         const AxisRec G1 = sload(rec, start + j1);
         AxisCore c;
         float D, r;
+        load_whole(G0);
         axis_core(G0, Q, c);
         pair_D(c, D, r);
         if (kStats) n_hitc += ballot(D <= k2) != 0 ? 1u : 0u;
@@ -75,6 +79,7 @@ __device__ inline void leaf_forward(const AxisRec *rec, const RunRay &Q, int64_t
             if (kStats) ++n_inc;
         }
         if (two) {
+            load_whole(G1);
             axis_core(G1, Q, c);
             pair_D(c, D, r);
             if (kStats) n_hitc += ballot(D <= k2) != 0 ? 1u : 0u;

@@ -140,6 +140,9 @@ __device__ inline void close_window(float (*part)[64], float (*res)[kSlots], flo
     __builtin_amdgcn_wave_barrier();
 }
 
+// The record's density loaded with the rest of it.
+__device__ inline void load_whole(const AxisRec &a) { asm volatile("" ::"s"(a.rho_c)); }
+
 // Both records of a traversal step held in scalar registers before either is
 // used, so that the step waits for memory once: the compiler otherwise issues
 // each record's loads at its first use, and the density's inside the branch
