@@ -11,7 +11,9 @@ namespace gr {
 constexpr uint32_t kMagic = 0x47524143u;  // "GRAC"
 constexpr int kDefaultLeaf = 64;
 constexpr int kDefaultHitCap = 8192;  // hit-list entries per wave (fused backward)
-constexpr int kSortTile = 4096;  // keys per radix-sort workgroup (256 threads x 16)
+constexpr int kSortTile = 1024;  // keys per radix-sort workgroup (256 threads x 4)
+constexpr int kSmallSort = 4096; // Gaussians up to which one workgroup sorts in LDS
+constexpr int kBoundsBlocks = 256;
 constexpr int kCullFields = 9;   // mean (3) + kappa^2 Sigma (6: xx yy zz xy xz yz)
 
 // Gaussian record, one per Gaussian in Morton order (80 bytes; a wave
@@ -65,8 +67,7 @@ static_assert(sizeof(GaussRec32) == 64, "GaussRec32 must be 64 bytes");
 struct alignas(64) Node {
     float b[12];
     int32_t child[2];
-    int32_t parent;
-    int32_t pad;
+    int32_t lo, hi;  // its leaves
 };
 static_assert(sizeof(Node) == 64, "Node must be 64 bytes");
 
@@ -101,7 +102,7 @@ struct Layout {
     int32_t level_count[kMaxLevels];
     int32_t level_off[kMaxLevels];
     int32_t wide_total;
-    size_t rec, rec32, axis, cull, nodes, aabb, keys0, keys1, vals0, vals1, hist, lparent, visit, wbox, total;
+    size_t rec, rec32, axis, cull, nodes, keys0, keys1, vals0, vals1, hist, totals, part, wbox, total;
 };
 
 __device__ __host__ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -121,14 +122,13 @@ inline Layout make_layout(int64_t n, int32_t leaf) {
     L.axis = off;    off = off + 3 * align256(nn * sizeof(AxisRec));
     L.cull = off;    off = align256(off + size_t(L.n_leaves) * leaf * kCullFields * sizeof(float));
     L.nodes = off;   off = align256(off + nodes * sizeof(Node));
-    L.aabb = off;    off = align256(off + nn * 6 * sizeof(float));
     L.keys0 = off;   off = align256(off + nn * 4);
     L.keys1 = off;   off = align256(off + nn * 4);
     L.vals0 = off;   off = align256(off + nn * 4);   // after sorting: Morton order -> input index
     L.vals1 = off;   off = align256(off + nn * 4);
     L.hist = off;    off = align256(off + size_t(256) * L.n_sort_blocks * 4);
-    L.lparent = off; off = align256(off + size_t(L.n_leaves) * 4);
-    L.visit = off;   off = align256(off + nodes * 4);
+    L.totals = off;  off = align256(off + size_t(256) * 4);
+    L.part = off;    off = align256(off + size_t(kBoundsBlocks) * 8 * 4);
     int32_t cnt = L.n_leaves, tot = 0, lv = 0;
     while (true) {
         L.level_count[lv] = cnt;
