@@ -84,21 +84,6 @@ __device__ inline T sload(const T *p, int64_t i) {
 #endif
 }
 
-// m without its r lowest set bits (0 <= r < popcount(m)): the position of the
-// r-th set bit by halving, then a mask.
-__device__ inline uint64_t drop_low_bits(uint64_t m, int r) {
-    uint64_t x = m;
-    int pos = 0;
-    for (int w = 32; w >= 1; w >>= 1) {
-        const int low = __builtin_popcountll(x & ((1ull << w) - 1ull));
-        const bool up = r >= low;
-        r = up ? r - low : r;
-        x = up ? x >> w : x;
-        pos = up ? pos + w : pos;
-    }
-    return m & (~0ull << pos);
-}
-
 // Inclusive prefix sum over the wave (lane k gets the sum of lanes 0..k):
 // shifts by 1, 2, 4, 8 within each row of 16 lanes, then the row totals
 // (row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3).
@@ -110,34 +95,6 @@ __device__ inline int wave_incl_scan(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
     return v;
-}
-
-// Closing step of a replay window whose pairs are split over the lanes in
-// consecutive ranges (the hit-list and TOF replays). A lane that moved on from
-// an entry inside its range has stored that entry's sums already; what is left
-// is each lane's sums c for the entry fe its range ends in (fe < 0: the lane
-// had no pairs). Lanes ending in the same entry are consecutive, since their
-// last pairs increase with the lane, so the first lane of each run adds the
-// run's sums to res[.][fe] with one read-modify-write and no LDS atomics;
-// part (10 x 64 floats, free by now) carries the other lanes' sums.
-template <int kSlots>
-__device__ inline void close_window(float (*part)[64], float (*res)[kSlots], float c[10], int fe, int lane) {
-    const int fe_prev = __shfl(fe, (lane + 63) & 63, 64);
-    const bool head = fe >= 0 && (lane == 0 || fe_prev != fe);
-    const uint64_t heads = ballot(head);
-    const int n_closing = __builtin_popcountll(ballot(fe >= 0));  // a prefix of the lanes
-    __builtin_amdgcn_wave_barrier();
-    if (fe >= 0 && !head)
-        for (int k = 0; k < 10; ++k) part[k][lane] = c[k];
-    __builtin_amdgcn_wave_barrier();
-    if (head) {
-        const uint64_t later = lane < 63 ? heads >> (lane + 1) : 0ull;
-        const int run_end = later ? lane + 1 + __builtin_ctzll(later) : n_closing;
-        for (int l = lane + 1; l < run_end; ++l)
-            for (int k = 0; k < 10; ++k) c[k] += part[k][l];
-        for (int k = 0; k < 10; ++k) res[k][fe] += c[k];
-    }
-    __builtin_amdgcn_wave_barrier();
 }
 
 // The record's density loaded with the rest of it.
@@ -393,43 +350,13 @@ __device__ inline bool slab(const float *b, const RayInv &R) {
 // the closed form for one (ray, Gaussian) pair
 // ---------------------------------------------------------------------------
 
-// d d^T products in the order the pair evaluation uses: xx yy zz 2xy 2xz 2yz.
-__device__ inline void ray_dd(const double d[3], double dd[6]) {
-    dd[0] = d[0] * d[0];
-    dd[1] = d[1] * d[1];
-    dd[2] = d[2] * d[2];
-    dd[3] = 2.0 * d[0] * d[1];
-    dd[4] = 2.0 * d[0] * d[2];
-    dd[5] = 2.0 * d[1] * d[2];
-}
-
-// Core of Eq. 7 for one pair, in FP64: delta, B, A and the numerator
-// N = C A - B^2 of D = N / A, from the ray and P (the replays' form).
-struct PairCore {
-    double dl[3];  // delta = o - mu
-    double B, A, N;
-};
-
-__device__ inline void pair_core(const double mu[3], const double P[6], const double o[3],
-                                 const double d[3], const double dd[6], PairCore &c) {
-    c.dl[0] = o[0] - mu[0];
-    c.dl[1] = o[1] - mu[1];
-    c.dl[2] = o[2] - mu[2];
-    const double px = fma(P[4], c.dl[2], fma(P[3], c.dl[1], P[0] * c.dl[0]));
-    const double py = fma(P[5], c.dl[2], fma(P[1], c.dl[1], P[3] * c.dl[0]));
-    const double pz = fma(P[2], c.dl[2], fma(P[5], c.dl[1], P[4] * c.dl[0]));
-    c.B = fma(d[2], pz, fma(d[1], py, d[0] * px));
-    const double C = fma(c.dl[2], pz, fma(c.dl[1], py, c.dl[0] * px));
-    c.A = fma(P[5], dd[5], fma(P[4], dd[4], fma(P[3], dd[3], fma(P[2], dd[2], fma(P[1], dd[1], P[0] * dd[0])))));
-    c.N = fma(C, c.A, -(c.B * c.B));
-}
-
-// The same A and N along a run's axis (Eq. 7 does not change when the origin
-// slides along the line): with the origin in the plane z = mk, e its offset
+// Core of Eq. 7 for one pair, in FP64: A and the numerator N = C A - B^2 of
+// D = N / A, along a run's axis. Eq. 7 does not change when the origin slides
+// along the line; with the origin in the plane z = mk, e its offset
 // from the mean there and g the direction less its conditional part, whitened
 // to (a, b) and (c, d): C = a^2 + b^2, A = c^2 + d^2 + h dk^2, B = a c + b d and,
 // by Lagrange's identity, N = C A - B^2 = (a d - b c)^2 + h dk^2 C. 21 FP64
-// operations instead of the general form's 26, from a record of the same size
+// operations instead of the 26 of A, B, C from P, from a record of the same size
 // and 16 instead of 24 registers of ray, and sums of squares in place of the
 // cancelling C A - B^2. The scale is Eq. 7's own, so A and N round to the same
 // FP32 values and the cutoff takes the same decisions. The forward is bound by
