@@ -204,6 +204,20 @@ __global__ __launch_bounds__(256) void k_bounds(const float *__restrict__ mean,
     if (threadIdx.x == 0) part[blockIdx.x] = b;
 }
 
+// Morton code of a valid mean inside the bounds.
+__device__ inline uint32_t mean_code(const float mu[3], const Bounds &b) {
+    uint32_t code = 0;
+    for (int k = 0; k < 3; ++k) {
+        float lo = ord2f(b.lo[k]), hi = ord2f(b.hi[k]);
+        if (!(hi > lo)) hi = lo + 1.0f;
+        float t = (mu[k] - lo) / (hi - lo);
+        int c = int(t * 1024.0f);
+        c = c < 0 ? 0 : (c > 1023 ? 1023 : c);
+        code |= spread10(uint32_t(c)) << (2 - k);
+    }
+    return code;
+}
+
 // 30-bit Morton code of the mean inside the valid-mean bounds; invalid
 // Gaussians get 0xFFFFFFFF and sort to the end.
 __device__ inline uint32_t morton_code(const float *__restrict__ mean, const float *__restrict__ scale,
@@ -211,16 +225,8 @@ __device__ inline uint32_t morton_code(const float *__restrict__ mean, const flo
                                        int64_t i, const Bounds &b) {
     double mu[3], s[3], q[4], rho;
     if (!load_params(mean, scale, quat, dens, n, i, mu, s, q, rho)) return 0xFFFFFFFFu;
-    uint32_t code = 0;
-    for (int k = 0; k < 3; ++k) {
-        float lo = ord2f(b.lo[k]), hi = ord2f(b.hi[k]);
-        if (!(hi > lo)) hi = lo + 1.0f;
-        float t = (float(mu[k]) - lo) / (hi - lo);
-        int c = int(t * 1024.0f);
-        c = c < 0 ? 0 : (c > 1023 ? 1023 : c);
-        code |= spread10(uint32_t(c)) << (2 - k);
-    }
-    return code;
+    const float m[3] = {float(mu[0]), float(mu[1]), float(mu[2])};
+    return mean_code(m, b);
 }
 
 // Codes of one sort tile, its first digit's histogram, and (block 0) the
@@ -253,47 +259,70 @@ __global__ __launch_bounds__(256) void k_codes(const float *__restrict__ mean, c
     hist[size_t(threadIdx.x) * gridDim.x + blockIdx.x] = h[threadIdx.x];
 }
 
-// Up to kSmallSort Gaussians: bounds, header, codes and the sort in one
-// workgroup. A bitonic sort of (code, input index) in LDS, which orders equal
-// codes as a stable sort does; exchanges over at most 64 places stay inside the
-// 128 elements of a wave and need no workgroup barrier. In place of 17 launches:
-// 512 Gaussians, bounds to sorted order, 85 us of kernels -> one of 14.5 us.
+// Up to kSmallSort Gaussians: bounds, header, codes and the sort of (code, input
+// index) in one launch. Every workgroup reads all Gaussians for the bounds and
+// the codes, and places 64 of them: a key's rank is the number of keys before
+// it, counted from LDS (each of the 16 waves counts one key in 16, which all its
+// lanes read at once), so nothing waits for another workgroup. Its reads and
+// compares grow with n^2 but stay spread over the chip, where sorting inside one
+// workgroup is bound by that compute unit's LDS (3,001 keys: this launch 15 us,
+// a bitonic sort 40 us, sorted runs merged by binary search 35-39 us).
+// A whole build takes, sorted here / by the radix sort's 13 launches:
+// 512 Gaussians 22 / 53 us, 3,001 30 / 64, 8,192 46 / 70, 12,000 57 / 71,
+// 16,000 66 / 72. The codes have to fit into the default 64 KB of LDS as well.
+constexpr uint32_t kLastCode = 0x40000000u;  // of an invalid Gaussian: after all 30-bit codes
 __global__ __launch_bounds__(1024) void k_sort_small(const float *__restrict__ mean, const float *__restrict__ scale,
                                                      const float *__restrict__ quat, const float *__restrict__ dens,
                                                      int32_t n, AccelHeader *hdr, int32_t leaf, int32_t n_leaves,
                                                      float kappa, uint32_t *__restrict__ keys,
                                                      uint32_t *__restrict__ vals) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t code[];  // n, rounded up to 64
     __shared__ Bounds lds[16];
-    __shared__ uint64_t e[kSmallSort];
-    const int t = threadIdx.x;
+    __shared__ int before[64];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int rows = (n + 63) >> 6;
     Bounds b;
     bounds_empty(b);
-    for (int i = t; i < n; i += 1024) bounds_add(b, mean, scale, quat, dens, n, i);
-    bounds_of_block(b, lds);
-    if (t == 0) write_header(hdr, n, leaf, n_leaves, kappa, b);
-    int m = 128;  // elements sorted: a power of 2
-    while (m < n) m *= 2;
-    for (int i = t; i < m; i += 1024)
-        e[i] = i < n ? (uint64_t(morton_code(mean, scale, quat, dens, n, i, b)) << 32) | uint32_t(i) : ~0ull;
-    __syncthreads();
-    for (int k = 2; k <= m; k *= 2)
-        for (int j = k / 2; j >= 1; j /= 2) {
-            for (int q = t; q < m / 2; q += 1024) {
-                const int i = ((q & ~(j - 1)) << 1) | (q & (j - 1));
-                const uint64_t x = e[i], y = e[i + j];
-                if ((x > y) == ((i & k) == 0)) {
-                    e[i] = y;
-                    e[i + j] = x;
-                }
-            }
-            // (the next exchange is over j / 2 places, or over k)
-            if (j > 64 || (j == 1 && k > 64)) __syncthreads();
-            else __builtin_amdgcn_wave_barrier();
-        }
-    __syncthreads();
+#pragma unroll 4
     for (int i = t; i < n; i += 1024) {
-        keys[i] = uint32_t(e[i] >> 32);
-        vals[i] = uint32_t(e[i]);
+        double mu[3], s[3], q4[4], rho;
+        const bool ok = load_params(mean, scale, quat, dens, n, i, mu, s, q4, rho);
+        b.bad += ok ? 0 : 1;
+        for (int k = 0; k < 3; ++k) {
+            const uint32_t u = f2ord(float(mu[k]));
+            b.lo[k] = min(b.lo[k], ok ? u : 0xFFFFFFFFu);
+            b.hi[k] = max(b.hi[k], ok ? u : 0u);
+        }
+        code[i] = ok ? 0u : kLastCode;
+    }
+    if (t < 64) before[t] = 0;
+    bounds_of_block(b, lds);
+    if (blockIdx.x == 0 && t == 0) write_header(hdr, n, leaf, n_leaves, kappa, b);
+#pragma unroll 4
+    for (int i = t; i < n; i += 1024) {  // each thread its own again
+        const float m[3] = {mean[i], mean[size_t(n) + i], mean[2 * size_t(n) + i]};
+        if (code[i] == 0u) code[i] = mean_code(m, b);
+    }
+    for (int i = n + t; i < rows * 64; i += 1024) code[i] = 0xFFFFFFFFu;
+    __syncthreads();
+    const int row = int(blockIdx.x), i = row * 64 + lane;
+    const uint32_t mine = code[i];
+    int c = 0;
+    for (int r = wave; r < rows; r += 16) {  // 64 keys of row r: equal ones of earlier rows go first
+        const uint32_t first = r < row ? mine + 1u : mine;  // (no overflow where it counts: i < n)
+#pragma unroll
+        for (int k = 0; k < 64; k += 4) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(code + r * 64 + k);
+            c += int(v.x < first) + int(v.y < first) + int(v.z < first) + int(v.w < first);
+        }
+        if (r == row)
+            for (int k = 0; k < 64; ++k) c += int(code[r * 64 + k] == mine && k < lane);
+    }
+    atomicAdd(&before[lane], c);
+    __syncthreads();
+    if (wave == 0 && i < n) {
+        keys[before[lane]] = mine == kLastCode ? 0xFFFFFFFFu : mine;
+        vals[before[lane]] = uint32_t(i);
     }
 }
 
@@ -777,8 +806,10 @@ hipError_t enqueue_build(const gr_scene &sc, const Layout &L, hipStream_t st) {
     uint32_t *v0 = reinterpret_cast<uint32_t *>(base + L.vals0);
     uint32_t *v1 = reinterpret_cast<uint32_t *>(base + L.vals1);
     if (n <= kSmallSort) {
-        k_sort_small<<<1, 1024, 0, st>>>(sc.mean, sc.scale, sc.quat, sc.density, int32_t(n), hdr, L.leaf, L.n_leaves,
-                                         sc.kappa, k0, v0);
+        const unsigned rows = unsigned((n + 63) / 64);
+        k_sort_small<<<rows, 1024, rows * 64 * sizeof(uint32_t), st>>>(sc.mean, sc.scale, sc.quat, sc.density,
+                                                                       int32_t(n), hdr, L.leaf, L.n_leaves, sc.kappa,
+                                                                       k0, v0);
     } else {
         uint32_t *hist = reinterpret_cast<uint32_t *>(base + L.hist);
         uint32_t *totals = reinterpret_cast<uint32_t *>(base + L.totals);

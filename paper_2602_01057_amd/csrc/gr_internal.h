@@ -12,7 +12,7 @@ constexpr uint32_t kMagic = 0x47524143u;  // "GRAC"
 constexpr int kDefaultLeaf = 64;
 constexpr int kDefaultHitCap = 8192;  // hit-list entries per wave (fused backward)
 constexpr int kSortTile = 1024;  // keys per radix-sort workgroup (256 threads x 4)
-constexpr int kSmallSort = 4096; // Gaussians up to which one workgroup sorts in LDS
+constexpr int kSmallSort = 12288;// Gaussians up to which one launch sorts by counting
 constexpr int kBoundsBlocks = 256;
 constexpr int kCullFields = 9;   // mean (3) + kappa^2 Sigma (6: xx yy zz xy xz yz)
 

@@ -142,7 +142,7 @@ inline unsigned launch_groups(int64_t items, const LaunchShape &shape) {
 }
 
 // Zero-fill kernels (capturable in a graph, unlike a memset node).
-void enqueue_zero_f32(float *p, int64_t count, hipStream_t st);
+void enqueue_zero_f32(float *p, int64_t count, hipStream_t st, uint32_t *counter = nullptr);
 void enqueue_zero_u32(uint32_t *p, hipStream_t st);
 // Chain rule from the 10 x n per-Gaussian sums (Morton order) to the raw
 // parameter gradients (input order).

@@ -617,10 +617,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void 
     }
 }
 
-// Zero the accumulators (a fill kernel, so the call stays capturable).
-__global__ void k_zero_f32(float *p, int64_t count) {
+// Zero the accumulators, and a launch's ticket counter with them (a fill
+// kernel, so the call stays capturable).
+__global__ void k_zero_f32(float *p, int64_t count, uint32_t *counter) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < count) p[i] = 0.0f;
+    if (counter && i == 0) *counter = 0u;
 }
 
 // Chain rule from the per-Gaussian sums (g_rho, m, M) to the raw
@@ -743,6 +745,7 @@ hipError_t enqueue_forward(LaunchTable &T, const LaunchShape &shape, hipStream_t
     return hipGetLastError();
 }
 
+// (the caller has zeroed the work counter)
 static void launch_backward(LaunchTable &T, const BwdArgs &A, const LaunchShape &shape, uint32_t *hit_g,
                             uint64_t *hit_m, hipStream_t st) {
     finish_table(T, shape);
@@ -751,7 +754,6 @@ static void launch_backward(LaunchTable &T, const BwdArgs &A, const LaunchShape 
     T.hit_g = lists ? hit_g : nullptr;
     T.hit_m = lists ? hit_m : nullptr;
     if (T.n_packets == 0) return;
-    if (shape.work_counter) k_zero_u32<<<1, 64, 0, st>>>(shape.work_counter);
     const int team = T.parts;
     if (team > 1 && lists && shape.free_groups) {
         // as many waves as the lists' regions were sized for
@@ -773,7 +775,10 @@ hipError_t enqueue_backward(LaunchTable &T, const BwdArgs &A, const gr_scene &sc
                             float *gmean, float *gscale, float *gquat, float *gdens,
                             const LaunchShape &shape, uint32_t *hit_g, uint64_t *hit_m,
                             hipStream_t st) {
-    enqueue_zero_f32(A.acc, 10 * sc.n, st);
+    if (sc.n > 0)
+        enqueue_zero_f32(A.acc, 10 * sc.n, st, shape.work_counter);
+    else if (shape.work_counter)
+        enqueue_zero_u32(shape.work_counter, st);
     launch_backward(T, A, shape, hit_g, hit_m, st);
     enqueue_epilogue(sc, order, A.acc, gmean, gscale, gquat, gdens, st);
     return hipGetLastError();
@@ -782,14 +787,15 @@ hipError_t enqueue_backward(LaunchTable &T, const BwdArgs &A, const gr_scene &sc
 hipError_t enqueue_fused_segments(LaunchTable &T, const LaunchShape &shape, uint32_t *hit_g, uint64_t *hit_m,
                                   hipStream_t st) {
     BwdArgs A{nullptr, nullptr};
+    if (shape.work_counter) enqueue_zero_u32(shape.work_counter, st);
     launch_backward(T, A, shape, hit_g, hit_m, st);
     return hipGetLastError();
 }
 
 void enqueue_zero_u32(uint32_t *p, hipStream_t st) { k_zero_u32<<<1, 64, 0, st>>>(p); }
 
-void enqueue_zero_f32(float *p, int64_t count, hipStream_t st) {
-    if (count > 0) k_zero_f32<<<unsigned((count + 255) / 256), 256, 0, st>>>(p, count);
+void enqueue_zero_f32(float *p, int64_t count, hipStream_t st, uint32_t *counter) {
+    if (count > 0) k_zero_f32<<<unsigned((count + 255) / 256), 256, 0, st>>>(p, count, counter);
 }
 
 void enqueue_epilogue(const gr_scene &sc, const uint32_t *order, const float *acc, float *gmean, float *gscale,

@@ -670,9 +670,11 @@ hipError_t enqueue_backward_tof(LaunchTable &T, const TofArgs &A, const gr_scene
                                 float *gmean, float *gscale, float *gquat, float *gdens, const LaunchShape &shape,
                                 hipStream_t st) {
     finish_table(T, shape);
-    enqueue_zero_f32(A.acc, 10 * sc.n, st);
+    if (sc.n > 0)
+        enqueue_zero_f32(A.acc, 10 * sc.n, st, shape.work_counter);
+    else if (shape.work_counter)
+        enqueue_zero_u32(shape.work_counter, st);
     if (T.n_packets > 0) {
-        if (shape.work_counter) enqueue_zero_u32(shape.work_counter, st);
         hipError_t e;
         switch (tof_bins_class(A.n_bins)) {
             case 1: e = launch_backward<1>(T, A, shape, st); break;

@@ -1,5 +1,5 @@
 """The acceleration structure at the sizes where its build changes form: the
-one-workgroup sort's last size and the first past it, sort tiles, leaves that do
+one-launch sort's last size and the first past it, sort tiles, leaves that do
 not fill a workgroup, two levels of the hierarchy above the one-workgroup top,
 equal codes and invalid Gaussians among them. Both traversals against the FP64
 oracle, after a build and after a refit of moved Gaussians."""
@@ -28,7 +28,8 @@ def _check(gr, S, sc, o, d, what):
 
 
 @pytest.mark.parametrize("n,leaf", [(1, 64), (64, 64), (65, 64), (127, 1), (129, 2), (1023, 48), (1025, 7), (4096, 64),
-                                    (4096, 1), (4097, 64), (5119, 33), (70_001, 1), (140_000, 64)])
+                                    (4096, 1), (4097, 64), (5119, 33), (12_288, 64), (12_289, 5), (70_001, 1),
+                                    (140_000, 64)])
 def test_build_and_refit_against_oracle(gr, n, leaf):
     rng = np.random.default_rng(n + leaf)
     hi = 9.0 * max(1.0, n / 500) ** -0.2
