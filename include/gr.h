@@ -470,8 +470,8 @@ gr_status gr_voxelize(const gr_scene *scene, const gr_grid *grid, float *out, co
  * (device, uint64, 8-byte aligned; the caller zeroes):
  *   [0] (voxel, Gaussian) pairs with D <= kappa^2: the unit of the
  *       voxelisation's throughput,
- *   [1] pairs evaluated (Gaussians whose kappa-box meets a 4x4x4 brick x the
- *       brick's voxels inside the grid).
+ *   [1] pairs evaluated (Gaussians whose kappa-ellipsoid may meet an 8x8x8
+ *       brick x the brick's voxels inside the grid).
  * out receives the same values as gr_voxelize. */
 gr_status gr_voxelize_stats(const gr_scene *scene, const gr_grid *grid, float *out, uint64_t *stats,
                             const gr_launch *opt, void *stream);

@@ -20,10 +20,11 @@ struct VoxGrid {
     int64_t bricks[3];  // bricks per axis
 };
 
-// Bricks of kBrick x kBrick x kBrickZ voxels: one wave each, lane (lx, ly) =
-// (lane % 8, lane / 8) holding the column of kBrickZ voxels along z.
+// Bricks of 8 x 8 x 8 voxels: one wave each, in eight octants of 4 x 4 x 4; lane
+// (lx, ly, lz) = (lane % 4, lane / 4 % 4, lane / 16) holds its voxel of every
+// octant. Octant s lies at 4 (s & 1, s >> 1 & 1, s >> 2) voxels.
 constexpr int kBrick = 8;
-constexpr int kBrickZ = 8;
+constexpr int kOct = 4;
 
 __device__ inline uint64_t ballot(bool p) { return __ballot(p); }
 
@@ -56,14 +57,25 @@ __device__ inline void level_info(int n_leaves, int lv, int &cnt, int &off) {
 
 constexpr int kStack = 64 * (kMaxLevels - 1);
 
-// One wave per brick of 8x8x8 voxels, each lane a column of 8 voxels along
-// z. The wide hierarchy is walked with box-versus-brick tests, 64 child boxes
-// per wave step; at a leaf the Gaussians are culled lane-parallel against the
-// brick, and the candidates' records (scalar loads) are evaluated at every
-// voxel: D = (x - mu)^T P (x - mu) in FP64 (along the column D is a quadratic
-// in z: D(t) = D0 + t (2 h (P delta0)_z) + t^2 h^2 P_zz), rho exp(-D/2) in
-// FP32, summed in FP64. With kStats, stats[0] += (voxel, Gaussian) pairs with
-// D <= kappa^2 and stats[1] += pairs evaluated (candidates x valid voxels).
+// One wave per brick of 8x8x8 voxels, each lane one voxel of every octant. The
+// wide hierarchy is walked with box-versus-brick tests, 64 child boxes per wave
+// step; at a leaf the Gaussians are culled lane-parallel against the brick, and
+// the candidates' records (scalar loads, the next one's under way meanwhile)
+// are evaluated at every voxel: D = (x - mu)^T P (x - mu) in FP64, at the other
+// octants from octant 0's by the quadratic's differences; where D <= kappa^2 in
+// any lane, rho exp(-D/2) in FP32, summed in FP64. With kStats, stats[0] +=
+// (voxel, Gaussian) pairs with D <= kappa^2 and stats[1] += pairs evaluated
+// (candidates x valid voxels).
+//
+// Bound by VALU issue (500,000 Gaussians with axes of 0.5-4 mm on 256^3 voxels:
+// 20k instructions per brick of 228 candidates, 77% of the time with the
+// exponentials at quarter rate). Most of a brick lies outside a candidate's
+// ellipsoid: it holds 0.16 of the voxels, and some voxel of 0.40 of the octants,
+// but of 0.54 of the brick's layers, so octants are what the exponential and the
+// sum are skipped for: 2.32 ms as columns without a skip, 1.99 with layers, 1.70
+// with octants. One inlined copy of the evaluation keeps the branches within 90
+// registers (three of them: 134, 2.6 ms). One / two waves per workgroup: 1.75 /
+// 1.72 ms; 6 waves per SIMD spill (1.84 ms).
 template <bool kStats>
 __global__ __launch_bounds__(256) void k_voxelize(SceneView S, VoxGrid G, float *__restrict__ out,
                                                  uint64_t *__restrict__ stats) {
@@ -75,19 +87,23 @@ __global__ __launch_bounds__(256) void k_voxelize(SceneView S, VoxGrid G, float 
     const int64_t nbx = G.bricks[0], nby = G.bricks[1], nbz = G.bricks[2];
     if (brick >= nbx * nby * nbz) return;
     const int64_t bx = brick % nbx, by = (brick / nbx) % nby, bz = brick / (nbx * nby);
-    const int64_t ix = bx * kBrick + (lane & 7), iy = by * kBrick + (lane >> 3), iz0 = bz * kBrickZ;
-    const bool xy_valid = ix < G.dims[0] && iy < G.dims[1];
-    const int nzv = int(G.dims[2] - iz0 < kBrickZ ? G.dims[2] - iz0 : kBrickZ);  // valid z in the brick
-    const double x[3] = {G.origin[0] + double(ix) * G.spacing[0], G.origin[1] + double(iy) * G.spacing[1],
-                         G.origin[2] + double(iz0) * G.spacing[2]};
-    const double hz = G.spacing[2];
+    const int64_t i0[3] = {bx * kBrick, by * kBrick, bz * kBrick};
+    const int64_t il[3] = {i0[0] + (lane & 3), i0[1] + (lane >> 2 & 3), i0[2] + (lane >> 4)};
+    uint32_t valid = 0;  // octants whose voxel of this lane lies in the grid
+    for (int s = 0; s < 8; ++s)
+        valid |= uint32_t(il[0] + kOct * (s & 1) < G.dims[0] && il[1] + kOct * (s >> 1 & 1) < G.dims[1] &&
+                          il[2] + kOct * (s >> 2) < G.dims[2])
+                 << s;
+    double x[3], step[3];  // the voxel of octant 0, and the octants' spacing
+    for (int k = 0; k < 3; ++k) {
+        x[k] = G.origin[k] + double(il[k]) * G.spacing[k];
+        step[k] = double(kOct) * G.spacing[k];
+    }
     // the brick's box (its valid voxels), padded
     float blo[3], bhi[3];
     {
-        const int64_t i0[3] = {bx * kBrick, by * kBrick, iz0};
         for (int k = 0; k < 3; ++k) {
-            const int64_t e = k == 2 ? kBrickZ : kBrick;
-            const int64_t i1 = (i0[k] + e - 1 < G.dims[k] ? i0[k] + e - 1 : G.dims[k] - 1);
+            const int64_t i1 = (i0[k] + kBrick - 1 < G.dims[k] ? i0[k] + kBrick - 1 : G.dims[k] - 1);
             const double a = G.origin[k] + double(i0[k]) * G.spacing[k];
             const double b = G.origin[k] + double(i1) * G.spacing[k];
             blo[k] = float(a) - kBoxPad - 1e-6f * fabsf(float(a));
@@ -102,8 +118,8 @@ __global__ __launch_bounds__(256) void k_voxelize(SceneView S, VoxGrid G, float 
         bc[k] = 0.5 * (double(blo[k]) + double(bhi[k]));
         be[k] = 0.5f * (bhi[k] - blo[k]) * 1.0001f;
     }
-    double acc[kBrickZ];
-    for (int t = 0; t < kBrickZ; ++t) acc[t] = 0.0;
+    double acc[8];
+    for (int s = 0; s < 8; ++s) acc[s] = 0.0;
     int32_t err = 0;
     uint32_t n_in = 0, n_eval = 0;
     const int top = S.n_levels - 1;
@@ -188,36 +204,40 @@ __global__ __launch_bounds__(256) void k_voxelize(SceneView S, VoxGrid G, float 
                     const double cy = fma(R.P[5], dz, fma(R.P[1], dy, R.P[3] * dx));
                     const double cz = fma(R.P[2], dz, fma(R.P[5], dy, R.P[4] * dx));
                     const double D0 = fma(dz, cz, fma(dy, cy, dx * cx));
-                    const double b1 = 2.0 * hz * cz, c2 = hz * hz * R.P[2];
+                    // D(x + step) = D + 2 step.c + step^T P step
+                    const double ax = fma(2.0 * step[0], cx, step[0] * step[0] * R.P[0]);
+                    const double ay = fma(2.0 * step[1], cy, step[1] * step[1] * R.P[1]);
+                    const double az = fma(2.0 * step[2], cz, step[2] * step[2] * R.P[2]);
+                    const double kyz = 2.0 * step[1] * step[2] * R.P[5];
+                    const double ay1 = fma(2.0 * step[0] * step[1], R.P[3], ay);  // at x + step x
+                    const double az1 = fma(2.0 * step[0] * step[2], R.P[4], az);
+                    const double D1 = D0 + ax, D2 = D0 + ay, D3 = D1 + ay1;
+                    const float Df[8] = {float(D0), float(D1), float(D2), float(D3),
+                                         float(D0 + az), float(D1 + az1), float(D2 + (az + kyz)),
+                                         float(D3 + (az1 + kyz))};
                     const float w = R.rho_c * kInvSqrt2Pi;
 #pragma unroll
-                    for (int t = 0; t < kBrickZ; ++t) {
-                        const double tt = double(t);
-                        const float Df = float(fma(fma(c2, tt, b1), tt, D0));
-                        const bool in = Df <= k2;
-                        const float e = w * __builtin_amdgcn_exp2f(-kHalfLog2e * Df);
-                        acc[t] += in ? double(e) : 0.0;
-                        if (kStats) {
-                            const bool v = xy_valid && t < nzv;
-                            n_eval += v;
-                            n_in += v && in;
-                        }
+                    for (int s = 0; s < 8; ++s) {
+                        const bool in = Df[s] <= k2;
+                        if (!ballot(in)) continue;  // (see above: 0.6 of the octants)
+                        const float e = w * __builtin_amdgcn_exp2f(-kHalfLog2e * Df[s]);
+                        acc[s] += double(in ? e : 0.0f);
+                        if (kStats) n_in += in && (valid >> s & 1u);
                     }
+                    if (kStats) n_eval += __builtin_popcount(valid);
                 };
-                // two records per step: both scalar loads are in flight at once
-                while (cm) {
-                    const int j0 = __builtin_ctzll(cm);
+                // the next record is loaded while one is evaluated
+                if (!cm) continue;
+                int j = __builtin_ctzll(cm);
+                GaussRec R = sload(S.rec, start + j);
+                while (true) {
                     cm &= cm - 1;
-                    const GaussRec R0 = sload(S.rec, start + j0);
-                    if (cm) {
-                        const int j1 = __builtin_ctzll(cm);
-                        cm &= cm - 1;
-                        const GaussRec R1 = sload(S.rec, start + j1);
-                        eval(R0);
-                        eval(R1);
-                    } else {
-                        eval(R0);
-                    }
+                    const int jn = cm ? __builtin_ctzll(cm) : j;
+                    const GaussRec N = sload(S.rec, start + jn);
+                    eval(R);
+                    if (!cm) break;
+                    R = N;
+                    j = jn;
                 }
             }
         } else {
@@ -235,8 +255,11 @@ __global__ __launch_bounds__(256) void k_voxelize(SceneView S, VoxGrid G, float 
         }
     }
     if (err && lane == 0) atomicOr(const_cast<int32_t *>(&S.hdr->flags), err);
-    if (xy_valid)
-        for (int t = 0; t < nzv; ++t) out[((iz0 + t) * G.dims[1] + iy) * G.dims[0] + ix] = float(acc[t]);
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+        if (valid >> s & 1u)
+            out[((il[2] + kOct * (s >> 2)) * G.dims[1] + il[1] + kOct * (s >> 1 & 1)) * G.dims[0] + il[0] +
+                kOct * (s & 1)] = float(acc[s]);
     if (kStats) {
         uint64_t a = n_in, b = n_eval;
         for (int o = 32; o > 0; o >>= 1) {
@@ -305,7 +328,7 @@ hipError_t enqueue_voxelize(const SceneView &S, const gr_grid &g, float *out, ui
         G.origin[k] = g.origin[k];
         G.spacing[k] = g.spacing[k];
         G.dims[k] = g.dims[k];
-        G.bricks[k] = (g.dims[k] + (k == 2 ? kBrickZ : kBrick) - 1) / (k == 2 ? kBrickZ : kBrick);
+        G.bricks[k] = (g.dims[k] + kBrick - 1) / kBrick;
     }
     const int64_t bricks = G.bricks[0] * G.bricks[1] * G.bricks[2];
     if (bricks == 0) return hipSuccess;
