@@ -64,7 +64,7 @@ PEAK_FP32_PACKED_TFLOPS = 157.3
 #            _FP32_TRANS) FLOPs (every lane of every issued instruction, idle
 #            lanes included) and SQ_INSTS_VALU wave-level instructions (one
 #            issues per SIMD every 4 cycles), for the fused and forward kernels.
-KERNEL_SOURCES = ["gr_project.hip", "gr_trace.h", "gr_launch.h", "gr_internal.h", "gr_api.hip"]
+KERNEL_SOURCES = ["gr_project.hip", "gr_trace.h", "gr_replay.h", "gr_launch.h", "gr_internal.h", "gr_api.hip"]
 COUNTERS: dict = {
     # profiles/fused_fwd_bwd_ct_cone_500k.md: mean over the full-size dispatches;
     # copy calibration FETCH x2.000, WRITE x1.000

@@ -242,6 +242,18 @@ __device__ __attribute__((always_inline)) inline void bins_until(int n, F &&f) {
     }
 }
 
+constexpr int kTeamRows = 16;  // bins whose sums the waves of a team exchange at a time
+
+// f(integral_constant<int, b>) for b = B, B + kTeamRows, ... below N and n.
+template <int B, int N, class F>
+__device__ __attribute__((always_inline)) inline void team_rows(int n, F &&f) {
+    if constexpr (B < N) {
+        if (B >= n) return;
+        f(std::integral_constant<int, B>{});
+        team_rows<B + kTeamRows, N>(n, f);
+    }
+}
+
 // The bins of one pair added to the line's FP64 sums: t* = -tn, s^2 =
 // sigma^2 + 1/A, and the chain of bin values (3 FP64 instructions per bin).
 template <int kBins>
@@ -268,9 +280,15 @@ __device__ __attribute__((always_inline)) inline void add_pair_bins(const TofBin
 }
 
 // One packet of the TOF forward: every lane takes the cutoff test of each
-// candidate for its line; the lanes inside it queue the pair for its bins.
-template <int kBins>
-__device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A, int64_t packet, int lane,
+// candidate for its line; the lanes inside it queue the pair for its bins. With
+// kTeam the workgroup's waves take one part of the packet's leaves each and
+// meet, run by run, in their queues (tof_wave_bytes_fwd apart), kTeamRows bins
+// at a time; the bins are summed and written by the waves in turn.
+static_assert(sizeof(double) * 64 * kTeamRows <= sizeof(TofQueue), "a wave's rows go into its queue");
+constexpr size_t tof_wave_bytes_fwd = sizeof(TofQueue) + sizeof(uint32_t) * kWideStack;
+
+template <int kBins, bool kTeam>
+__device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A, int64_t packet, int lane, int wave,
                                           uint32_t *stack, TofQueue &Q) {
     PacketRef P;
     if (!locate_packet(T, packet, lane, P)) return;
@@ -333,7 +351,7 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
             }
         }
     };
-    traverse_run(T.traversal, S, R, B, in, lane, stack, Part{0, 0}, [&](int l) {
+    traverse_run(T.traversal, S, R, B, in, lane, stack, kTeam ? Part{T.parts - 1, wave} : Part{0, 0}, [&](int l) {
         int64_t start;
         uint64_t mask = leaf_candidates(S, B, l, lane, start);
         // two candidates per step (their records load together)
@@ -360,7 +378,24 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
         }
     });
     while (ballot(cnt > 0)) bin_step();
-    if (in) {
+    if constexpr (kTeam) {
+        const int n = tof ? tb.nb : 1;
+        const float att = in ? ray_atten(A, P.ray) : 0.0f;
+        double *mine = reinterpret_cast<double *>(&Q) + lane;
+        const char *first = reinterpret_cast<const char *>(&Q) - size_t(wave) * tof_wave_bytes_fwd;
+        team_rows<0, kBins>(n, [&](auto row0) {
+            constexpr int kEnd = row0 + kTeamRows < kBins ? row0 + kTeamRows : kBins;
+            bins_until<row0, kEnd>(n, [&](auto b) { mine[64 * (b - row0)] = acc[b]; });
+            __syncthreads();
+            for (int b = row0 + wave; b < row0 + kTeamRows && b < n; b += T.parts) {
+                double t = 0.0;
+                for (int k = 0; k < T.parts; ++k)
+                    t += reinterpret_cast<const double *>(first + size_t(k) * tof_wave_bytes_fwd)[64 * (b - row0) + lane];
+                if (in) A.out[int64_t(b) * A.n_rays + P.out] = float(double(att) * t);
+            }
+            __syncthreads();
+        });
+    } else if (in) {
         const float att = ray_atten(A, P.ray);
         // (opaque values: otherwise the bins' offsets and masks are all held
         // through the traversal)
@@ -375,7 +410,7 @@ __device__ inline void packet_forward_tof(const LaunchTable &T, const TofArgs &A
     }
     }
     // no line (zero or not finite), or no scene
-    if (((all & ~lines) >> lane) & 1ull)
+    if ((!kTeam || wave == 0) && ((all & ~lines) >> lane) & 1ull)
         for (int b = 0; b < (tof ? tb.nb : 1); ++b) A.out[int64_t(b) * A.n_rays + P.out] = 0.0f * ray_atten(A, P.ray);
 }
 
@@ -385,15 +420,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kBins > 16 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     // per wave: the queue, then the traversal stack
-    unsigned char *base = tof_lds + size_t(wave) * (sizeof(TofQueue) + sizeof(uint32_t) * kWideStack);
+    unsigned char *base = tof_lds + size_t(wave) * tof_wave_bytes_fwd;
     TofQueue &Q = *reinterpret_cast<TofQueue *>(base);
     uint32_t *stack = reinterpret_cast<uint32_t *>(base + sizeof(TofQueue));
     const bool pull = T.work_counter != nullptr;
     int64_t packet = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
     while (packet < T.n_packets) {
-        packet_forward_tof<kBins>(T, A, packet, lane, stack, Q);
+        packet_forward_tof<kBins, false>(T, A, packet, lane, wave, stack, Q);
         packet = pull ? next_packet(T.work_counter, lane) : T.n_packets;
     }
+}
+
+// The same for a launch of few packets: one packet per workgroup, one wave per
+// part (at most kTofTeam: the registers of more waves would not fit together).
+constexpr int kTofTeam = 4;
+template <int kBins>
+__global__ __launch_bounds__(64 * kTofTeam) __attribute__((amdgpu_waves_per_eu(kBins > 16 ? 3 : 4))) void k_forward_tof_team(LaunchTable T, TofArgs A) {
+    extern __shared__ __align__(16) unsigned char tof_lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    unsigned char *base = tof_lds + size_t(wave) * tof_wave_bytes_fwd;
+    packet_forward_tof<kBins, true>(T, A, logical_block(T.xcd_remap), lane, wave,
+                                    reinterpret_cast<uint32_t *>(base + sizeof(TofQueue)),
+                                    *reinterpret_cast<TofQueue *>(base));
 }
 
 // Gradient sums of one (ray, Gaussian) pair with the ray's bin weights wi[64 b],
@@ -627,10 +676,34 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_weights(int32_t kind, con
     }
 }
 
+// Parts of a packet in the TOF forward (packet_parts is the plain kernels' rule):
+// its sums take registers that leave 3 waves per SIMD, so the chip is full from
+// 3,072 waves on and a team meets over every run's bins. Measured (us, whole / 2 /
+// 4 parts, packets of 64 lines, 25 bins):
+//   512 Gaussians, 64 packets 20 / 22 / 19, 512 packets 22 / 27 / 26;
+//   5,000, 512 packets 56 / 52 / 43, 2,048 packets 73 / 90 / 102;
+//   50,000, 64 packets 289 / 188 / 130, 2,048 packets 446 / 441 / 442, 8,192
+//   1159 / 1198 / 1407;
+//   200,000, 64 packets 1287 / 722 / 423, 2,048 packets 1672 / 1557 / 1370, 8,192
+//   4754 / 4455 / 4606, 16,384 8266 / 8289 / 8871;
+// which waves = parts x packets up to 300 sqrt(leaves) follows.
+inline int tof_parts(int64_t packets, int32_t n_leaves) {
+    int parts = kTofTeam;
+    while (parts > 1 && (parts > n_leaves || double(packets) * parts > 300.0 * sqrt(double(n_leaves)))) parts /= 2;
+    return parts;
+}
+
 template <int kBins>
 hipError_t launch_forward(LaunchTable &T, const TofArgs &A, const LaunchShape &shape, hipStream_t st) {
+    T.parts = tof_parts(T.n_packets, T.scenes[T.segs[0].scene].n_leaves);
+    if (T.parts > 1 && shape.free_waves && !shape.work_counter) {
+        T.waves_per_group = T.parts;
+        k_forward_tof_team<kBins><<<dim3(unsigned(T.n_packets)), dim3(64 * T.parts),
+                                    tof_wave_bytes_fwd * size_t(T.parts), st>>>(T, A);
+        return hipGetLastError();
+    }
     const unsigned groups = launch_groups(T.n_packets, shape);
-    const size_t lds = (sizeof(TofQueue) + sizeof(uint32_t) * kWideStack) * size_t(shape.waves);
+    const size_t lds = tof_wave_bytes_fwd * size_t(shape.waves);
     k_forward_tof<kBins><<<dim3(groups), dim3(64 * shape.waves), lds, st>>>(T, A);
     return hipGetLastError();
 }

@@ -9,6 +9,7 @@ import oracle
 from oracle import geometry as G
 from paper_2602_01057_amd.inputs import sample_scene, sample_unit_weights
 from parity import assert_forward, assert_grad, gpu_grad_rows
+from test_gpu_tof import assert_bins
 
 pytestmark = pytest.mark.gpu
 
@@ -67,4 +68,32 @@ def test_parts_against_oracle_and_whole_packets(gr, n, leaf, views, nu, nv):
     want = oracle.grad_tof(sc, o, d, np.stack([w, -w, 0.5 * w]).astype(np.float64), 3, 40.0, 60.0)
     got = gr.project_tof_backward(S, ro, rd, _dev(np.stack([w, -w, np.float32(0.5) * w])), 3, sigma=40.0, bin_width=60.0)
     assert_grad(gpu_grad_rows(got, idx), want, what="tof backward")
+    assert S.status_flags() == 0
+
+
+# (leaf size: scenes of 20, 313 and 1 leaves): TOF forward of few packets, whose leaves are dealt out to the waves of
+# a workgroup; one bin, bin counts on and past the rows exchanged at a time, and lines with nothing in reach
+@pytest.mark.parametrize("n,leaf", [(320, 16), (313, 1), (60, 64)])
+@pytest.mark.parametrize("bins", [0, 1, 15, 16, 17, 32])
+def test_tof_forward_parts_against_oracle(gr, n, leaf, bins):
+    import torch
+    sc = sample_scene(n, seed=5 + n, radius=60.0, scale_range=(1.0, 9.0))
+    rng = np.random.default_rng(n + bins)
+    m = 64 * 12 + 17
+    o = rng.uniform(-30, 30, (3, m)).astype(np.float32)
+    d = rng.standard_normal((3, m)).astype(np.float32)
+    d /= np.linalg.norm(d, axis=0)
+    o[:, 64:128] = o[:, 64:65]
+    d[:, 64:128] = d[:, 64:65] + np.float32(0.02) * d[:, 64:128]   # one coherent packet among scattered lines
+    o[:, 200:210] += 500.0 * np.cross(d[:, 200:210], [0, 0, 1], axis=0)
+    c = rng.uniform(-10, 10, m).astype(np.float32)
+    att = rng.uniform(0.2, 1.0, m).astype(np.float32)
+    sigma, width = 12.0, 9.0
+    S = gr.Scene(*[_dev(a) for a in (sc.mean, sc.scale, sc.quat, sc.density)], leaf_size=leaf)
+    kw = dict(center=_dev(c), atten=_dev(att))
+    got = gr.project_tof(S, _dev(o), _dev(d), bins, sigma=sigma, bin_width=width, **kw)
+    one = gr.project_tof(S, _dev(o), _dev(d), bins, sigma=sigma, bin_width=width, waves_per_group=2, **kw)
+    ref = oracle.project_tof(sc, o, d, bins, sigma, width, center=c, atten=att)
+    assert_bins(got.cpu().numpy(), ref, f"{n} Gaussians, {bins} bins")
+    assert torch.allclose(got, one, rtol=LAST_BIT, atol=1e-37)
     assert S.status_flags() == 0
