@@ -102,9 +102,9 @@ gr_status gr_accel_bytes(int64_t n, int32_t leaf_size, size_t *bytes /* host */)
 /* Builds the acceleration structure on the device, all on `stream`:
  * per-Gaussian preprocessing (rotation, whitening, kappa-sigma boxes,
  * validity), 30-bit Morton codes of the means inside the scene bounds, a
- * stable LSD radix sort, a Karras radix-tree LBVH over leaves of leaf_size
- * Gaussians with a bottom-up refit of the node boxes, and a 64-wide
- * hierarchy of boxes over the same Morton-ordered leaves. Gaussians with s <= 0,
+ * stable sort of them, a Karras radix-tree LBVH over leaves of leaf_size
+ * Gaussians, and a 64-wide hierarchy of boxes over the same Morton-ordered
+ * leaves. Gaussians with s <= 0,
  * q = 0 or non-finite values are counted and excluded from every result. */
 gr_status gr_build_accel(const gr_scene *scene, void *stream);
 
@@ -418,8 +418,8 @@ typedef struct gr_ct_geom {
  * planes), so that its tiles hold as many rays as the others. Packets are 64
  * consecutive rays: tiles of exactly 64 rays (tile_radial x tile_axial x
  * tile_views = 64, with n_radial and the plane count multiples of the tile)
- * keep every packet inside one tile; a packet that straddles two tiles can
- * span distant planes and runs far slower. 8 radial x 1 plane x 8 views holds
+ * keep every packet inside one tile; a packet that straddles two tiles is
+ * traced as two stretches of rays, each at the cost of a packet. 8 radial x 1 plane x 8 views holds
  * nearly coincident lines where they pass closest to the centre and runs the
  * 200k-Gaussian PET workload about twice as fast as 8 x 8 x 1. */
 typedef struct gr_pet_geom {

@@ -1,12 +1,12 @@
 // Acceleration-structure build: per-Gaussian preprocessing, Morton codes,
-// stable LSD radix sort, records and leaf boxes, the wide hierarchy, Karras
+// counting or stable LSD radix sort, records and leaf boxes, the wide hierarchy, Karras
 // radix-tree LBVH over leaves of L Gaussians. Everything runs on one stream with
 // no host round trip.
 //
 // A build is a chain of short kernels, so it is bound by their number and by
 // each one's longest dependent chain, not by bandwidth (500k Gaussians move
-// about 0.25 GB, 50 us): up to 4,096 Gaussians are coded and sorted by one
-// workgroup, the boxes of the leaves come out of the record kernel's LDS, the
+// about 0.25 GB, 50 us): up to 12,288 Gaussians are coded and sorted in one
+// launch, the boxes of the leaves come out of the record kernel's LDS, the
 // upper levels of the hierarchy are one launch, and a binary node's boxes are
 // read off the hierarchy's levels by a wave of its own instead of climbing the
 // tree leaf by leaf with atomics.
