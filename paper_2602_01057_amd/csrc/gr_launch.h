@@ -114,6 +114,14 @@ hipError_t enqueue_backward(LaunchTable &T, const BwdArgs &A, const gr_scene &sc
 hipError_t enqueue_fused_segments(LaunchTable &T, const LaunchShape &shape, uint32_t *hit_g, uint64_t *hit_m,
                                   hipStream_t st);
 
+// Leaves of the largest scene of the launch.
+inline int32_t most_leaves(const LaunchTable &T) {
+    int32_t leaves = 1;
+    for (int s = 0; s < T.n_segs; ++s)
+        if (T.scenes[T.segs[s].scene].n_leaves > leaves) leaves = T.scenes[T.segs[s].scene].n_leaves;
+    return leaves;
+}
+
 // Packet numbering of the segments and the launch shape, filled in before a
 // launch.
 inline void finish_table(LaunchTable &T, const LaunchShape &shape) {
@@ -123,10 +131,7 @@ inline void finish_table(LaunchTable &T, const LaunchShape &shape) {
         pk += (T.segs[s].n_rays + 63) / 64;
     }
     T.n_packets = pk;
-    int32_t leaves = 1;
-    for (int s = 0; s < T.n_segs; ++s)
-        if (T.scenes[T.segs[s].scene].n_leaves > leaves) leaves = T.scenes[T.segs[s].scene].n_leaves;
-    T.parts = packet_parts(pk, leaves);
+    T.parts = packet_parts(pk, most_leaves(T));
     T.waves_per_group = shape.waves;
     T.xcd_remap = shape.remap;
     T.persistent_groups = shape.persistent_groups;

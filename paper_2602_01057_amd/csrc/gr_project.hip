@@ -47,8 +47,8 @@ namespace gr {
 // kernels
 // ---------------------------------------------------------------------------
 
-// Forward sum over one leaf's candidate Gaussians (mask), two records per
-// step. The compiler issues each record's scalar loads at its first use; the 8
+// Forward sum over up to 64 candidate Gaussians (mask, at(bit) their position),
+// two records per step. The compiler issues each record's scalar loads at its first use; the 8
 // waves per SIMD of k_forward hide that latency. The density is taken with the
 // record (load_whole): inside the branch of the lanes within the cutoff, where
 // the compiler would put it, it is a second wait per pair (50k Gaussians, 50
@@ -56,9 +56,9 @@ namespace gr {
 // scene the same). Holding both records before the first evaluation
 // (hold_records, as the recording loop of the fused pass does) is slower here:
 // 1873 us, more scalar registers spill at 8 waves.
-template <bool kStats>
-__device__ inline void leaf_forward(const AxisRec *rec, const RunRay &Q, int64_t start, uint64_t mask,
-                                    double &acc, uint32_t &n_inc, uint32_t &n_hitc) {
+template <bool kStats, class At>
+__device__ inline void leaf_forward(const AxisRec *rec, const RunRay &Q, uint64_t mask, At &&at, double &acc,
+                                    uint32_t &n_inc, uint32_t &n_hitc) {
     const float k2 = Q.cut;
     while (mask) {
         const int j0 = __builtin_ctzll(mask);
@@ -66,8 +66,8 @@ __device__ inline void leaf_forward(const AxisRec *rec, const RunRay &Q, int64_t
         const bool two = mask != 0;
         const int j1 = two ? __builtin_ctzll(mask) : j0;
         if (two) mask &= mask - 1;
-        const AxisRec G0 = sload(rec, start + j0);
-        const AxisRec G1 = sload(rec, start + j1);
+        const AxisRec G0 = sload(rec, at(j0));
+        const AxisRec G1 = sload(rec, at(j1));
         AxisCore c;
         float D, r;
         load_whole(G0);
@@ -123,10 +123,9 @@ __device__ inline void pair_core32(const GaussRec32 &G, const Ray &R, float inv_
 }
 
 // leaf_forward in the FP32 precision mode (compact records, two per step).
-template <bool kStats>
-__device__ inline void leaf_forward32(const SceneView &S, const Ray &R, float inv_dd, int64_t start,
-                                      uint64_t mask, float k2, double &acc, uint32_t &n_inc,
-                                      uint32_t &n_hitc) {
+template <bool kStats, class At>
+__device__ inline void leaf_forward32(const SceneView &S, const Ray &R, float inv_dd, uint64_t mask, At &&at,
+                                      float k2, double &acc, uint32_t &n_inc, uint32_t &n_hitc) {
     while (mask) {
         const int j0 = __builtin_ctzll(mask);
         mask &= mask - 1;
@@ -134,8 +133,8 @@ __device__ inline void leaf_forward32(const SceneView &S, const Ray &R, float in
         const int j1 = two ? __builtin_ctzll(mask) : j0;
         if (two) mask &= mask - 1;
         const GaussRec32 *rec32 = rec32_of(S);
-        const GaussRec32 G0 = sload(rec32, start + j0);
-        const GaussRec32 G1 = sload(rec32, start + j1);
+        const GaussRec32 G0 = sload(rec32, at(j0));
+        const GaussRec32 G1 = sload(rec32, at(j1));
         float D, r;
         pair_core32(G0, R, inv_dd, D, r);
         if (kStats) n_hitc += ballot(D <= k2) != 0 ? 1u : 0u;
@@ -157,10 +156,28 @@ __device__ inline void leaf_forward32(const SceneView &S, const Ray &R, float in
 // One packet of the forward pass. kStats adds work counters (atomics once per
 // packet) for measurement runs; the production instantiation has none.
 // kCompact selects the FP32 precision mode. With kTeam the workgroup's waves
-// take one part each and meet in `sums` (64 per wave).
-template <bool kStats, bool kCompact, bool kTeam>
+// take one part of the leaves each and meet in `team`.
+//
+// Where a wave has few leaves, its own can hold a multiple of another's
+// candidates, and the packet waits for it: then the waves list their candidates
+// and evaluate the packet's in equal shares, in an order that does not depend on
+// timing. With many leaves per wave the shares are even by themselves and only
+// the phases' barriers are felt, likewise for a packet of several runs. Measured,
+// own leaves / shared, us: 3,001 Gaussians, one view of 64 x 64 29.2 / 23.4, of
+// 61 x 47 (several runs) 47.4 / 52.0; 5,000, 64 packets 39.7 / 33.1, 1,024 64.4 /
+// 53.4; 20,000, six views of 200 x 152 (8 parts) 168 / 157, 64 packets (16 parts)
+// 73.7 / 76.3; 50,000, 256 packets 146 / 158.
+constexpr int kTeamList = 512;  // candidates a wave lists; past it, it evaluates its own
+inline bool share_candidates(int parts, int32_t n_leaves) { return n_leaves <= (parts == kMaxParts ? 128 : 512); }
+struct TeamLds {
+    double *sums;     // [waves][64]
+    uint32_t *list;   // [waves][kTeamList]
+    uint32_t *count;  // [waves]
+};
+
+template <bool kStats, bool kCompact, bool kTeam, bool kShare = false>
 __device__ inline void packet_forward(const LaunchTable &T, int64_t packet, int lane, int wave, uint32_t *stack,
-                                      double *sums, uint64_t *stats) {
+                                      const TeamLds &team, uint64_t *stats) {
     PacketRef P;
     if (!locate_packet(T, packet, lane, P)) return;
     const Segment &sg = T.segs[P.seg];
@@ -172,7 +189,16 @@ __device__ inline void packet_forward(const LaunchTable &T, int64_t packet, int 
     uint32_t n_inc = 0, n_cand = 0, n_leaf = 0, n_hitc = 0;
     const float inv_dd = kCompact ? 1.0f / (R.d[0] * R.d[0] + R.d[1] * R.d[1] + R.d[2] * R.d[2]) : 0.0f;
     const Part part = kTeam ? Part{T.parts - 1, wave} : Part{0, 0};
-    for_runs(S, R, ballot(P.active), lane, [&](bool in, const RunRay &Q, const Beam &B) {
+    const uint64_t active = ballot(P.active);
+    for_runs(S, R, active, lane, [&](bool in, const RunRay &Q, const Beam &B) {
+        const bool share = kShare && ballot(in) == active;
+        auto evaluate = [&](uint64_t mask, auto &&at) {
+            if constexpr (kCompact)
+                leaf_forward32<kStats>(S, R, inv_dd, mask, at, Q.cut, total, n_inc, n_hitc);
+            else
+                leaf_forward<kStats>(B.rec, Q, mask, at, total, n_inc, n_hitc);
+        };
+        int listed = 0;
         traverse_run(T.traversal, S, R, B, in, lane, stack, part, [&](int l) {
             int64_t start;
             const uint64_t mask = leaf_candidates(S, B, l, lane, start);
@@ -180,17 +206,44 @@ __device__ inline void packet_forward(const LaunchTable &T, int64_t packet, int 
                 ++n_leaf;
                 n_cand += __builtin_popcountll(mask);
             }
-            if constexpr (kCompact)
-                leaf_forward32<kStats>(S, R, inv_dd, start, mask, Q.cut, total, n_inc, n_hitc);
-            else
-                leaf_forward<kStats>(B.rec, Q, start, mask, total, n_inc, n_hitc);
+            const int nc = kShare ? __builtin_popcountll(mask) : 0;
+            if (kShare && share && listed + nc <= kTeamList) {
+                if ((mask >> lane) & 1ull)
+                    team.list[wave * kTeamList + listed + __builtin_popcountll(mask & ((1ull << lane) - 1ull))] =
+                        uint32_t(start + lane);
+                listed += nc;
+            } else {
+                evaluate(mask, [&](int j) { return start + j; });
+            }
         });
+        if (kShare && share) {
+            if (lane == 0) team.count[wave] = uint32_t(listed);
+            __syncthreads();
+            // candidate q of the run is this wave's when q mod parts is the wave
+            const int cnt = lane < T.parts ? int(team.count[lane]) : 0;
+            int upto = cnt;  // lane p: candidates listed by waves 0 .. p
+            for (int o = 1; o < T.parts; o *= 2) {
+                const int v = __shfl_up(upto, o, 64);
+                if (lane >= o) upto += v;
+            }
+            const int all = __builtin_amdgcn_readlane(upto, T.parts - 1);
+            for (int q0 = wave; q0 < all; q0 += 64 * T.parts) {
+                const int q = q0 + lane * T.parts;
+                const bool mine = q < all;
+                int w = 0;  // the wave that listed q
+                for (int p = 0; p < T.parts - 1; ++p) w += __builtin_amdgcn_readlane(upto, p) <= q;
+                const int first = __shfl(upto - cnt, w, 64);
+                const int idx = mine ? int(team.list[w * kTeamList + q - first]) : 0;
+                evaluate(ballot(mine), [&](int j) { return int64_t(__builtin_amdgcn_readlane(idx, j)); });
+            }
+            __syncthreads();  // the lists are read
+        }
     });
     if (kTeam) {
-        sums[wave * 64 + lane] = total;
+        team.sums[wave * 64 + lane] = total;
         __syncthreads();
         if (wave != 0) return;
-        for (int k = 1; k < T.parts; ++k) total += sums[k * 64 + lane];
+        for (int k = 1; k < T.parts; ++k) total += team.sums[k * 64 + lane];
     }
     if (P.active) out[P.out] = float(total);
     if (kStats) {
@@ -226,21 +279,25 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     const bool pull = T.work_counter != nullptr;
     int64_t packet = pull ? next_packet(T.work_counter, lane) : logical_block(T.xcd_remap) * T.waves_per_group + wave;
     while (packet < T.n_packets) {
-        packet_forward<kStats, kCompact, false>(T, packet, lane, 0, stack, nullptr, stats);
+        packet_forward<kStats, kCompact, false>(T, packet, lane, 0, stack, TeamLds{}, stats);
         packet = pull ? next_packet(T.work_counter, lane) : T.n_packets;
     }
 }
 
 // The forward of a launch of few packets: one workgroup per packet, one wave
 // per part.
-template <bool kCompact>
+template <bool kCompact, bool kShare>
 __global__ __launch_bounds__(1024) void k_forward_team(LaunchTable T) {
-    extern __shared__ __align__(16) unsigned char team_lds[];  // 64 sums, then kWideStack entries per wave
+    extern __shared__ __align__(16) unsigned char team_lds[];  // per wave 64 sums, kWideStack entries, kTeamList, a count
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-    double *sums = reinterpret_cast<double *>(team_lds);
-    uint32_t *stack = reinterpret_cast<uint32_t *>(sums + 64 * T.waves_per_group) + wave * kWideStack;
-    packet_forward<false, kCompact, true>(T, logical_block(T.xcd_remap), lane, wave, stack, sums, nullptr);
+    TeamLds team;
+    team.sums = reinterpret_cast<double *>(team_lds);
+    uint32_t *stacks = reinterpret_cast<uint32_t *>(team.sums + 64 * T.waves_per_group);
+    team.list = stacks + kWideStack * T.waves_per_group;
+    team.count = team.list + kTeamList * T.waves_per_group;
+    packet_forward<false, kCompact, true, kShare>(T, logical_block(T.xcd_remap), lane, wave, stacks + wave * kWideStack, team,
+                                          nullptr);
 }
 
 // A ray as its lane holds it for the replay of its run: the line across the
@@ -730,11 +787,11 @@ hipError_t enqueue_forward(LaunchTable &T, const LaunchShape &shape, hipStream_t
     const int team = T.parts;
     if (team > 1 && shape.free_waves && !shape.work_counter && !stats) {
         T.waves_per_group = team;
-        const size_t lds = (sizeof(double) * 64 + sizeof(uint32_t) * kWideStack) * size_t(team);
-        if (T.precision == 1)
-            k_forward_team<true><<<dim3(unsigned(T.n_packets)), dim3(64 * team), lds, st>>>(T);
-        else
-            k_forward_team<false><<<dim3(unsigned(T.n_packets)), dim3(64 * team), lds, st>>>(T);
+        const bool share = share_candidates(team, most_leaves(T));
+        const size_t lds = (sizeof(double) * 64 + sizeof(uint32_t) * (kWideStack + (share ? kTeamList + 1 : 0))) * size_t(team);
+        auto kernel = T.precision == 1 ? (share ? k_forward_team<true, true> : k_forward_team<true, false>)
+                                       : (share ? k_forward_team<false, true> : k_forward_team<false, false>);
+        kernel<<<dim3(unsigned(T.n_packets)), dim3(64 * team), lds, st>>>(T);
         return hipGetLastError();
     }
     const unsigned groups = launch_groups(T.n_packets, shape);

@@ -97,3 +97,24 @@ def test_tof_forward_parts_against_oracle(gr, n, leaf, bins):
     assert_bins(got.cpu().numpy(), ref, f"{n} Gaussians, {bins} bins")
     assert torch.allclose(got, one, rtol=LAST_BIT, atol=1e-37)
     assert S.status_flags() == 0
+
+
+# (Gaussians, leaf size, scales, views): one coarse view whose packet has more candidates per wave than it lists
+# (listed and own evaluations mixed), the most leaves that are shared by 16 and by fewer parts and one more
+@pytest.mark.parametrize("n,leaf,views,nu", [(8192, 64, 1, 8), (128 * 4, 4, 1, 16), (128 * 4 + 1, 4, 1, 16),
+                                             (1024, 2, 40, 40), (1026, 2, 40, 40), (2, 1, 1, 8)])
+def test_shared_candidates_against_oracle(gr, n, leaf, views, nu):
+    import torch
+    sc = sample_scene(n, seed=3 + n, radius=60.0, scale_range=(1.0, 9.0))
+    g = dict(kind="ct", cone=1, n_views=views, nu=nu, nv=nu, angle0=0.1, angle_range=5.0, dso=400.0, dsd=700.0,
+             pitch_u=190.0 / nu, pitch_v=190.0 / nu, offset_u=0.0, offset_v=0.0, tile_u=8, tile_v=8)
+    o, d = G.rays32(g)
+    S = gr.Scene(*[_dev(a) for a in (sc.mean, sc.scale, sc.quat, sc.density)], leaf_size=leaf)
+    I = gr.project(S, _dev(o), _dev(d))
+    assert_forward(I.cpu().numpy(), oracle.project(sc, o, d), what=f"{n} {leaf}")
+    for kw in (dict(), dict(traversal=1), dict(precision="fp32")):
+        a = gr.project(S, _dev(o), _dev(d), **kw)
+        assert a.cpu().numpy().tobytes() == gr.project(S, _dev(o), _dev(d), **kw).cpu().numpy().tobytes(), kw
+        b = gr.project(S, _dev(o), _dev(d), waves_per_group=2, **kw)
+        assert torch.allclose(a, b, rtol=LAST_BIT, atol=0.0), kw
+    assert S.status_flags() == 0
