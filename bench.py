@@ -68,18 +68,18 @@ KERNEL_SOURCES = ["gr_project.hip", "gr_trace.h", "gr_replay.h", "gr_launch.h", 
 COUNTERS: dict = {
     # profiles/fused_fwd_bwd_ct_cone_500k.md: mean over the full-size dispatches;
     # copy calibration FETCH x2.000, WRITE x1.000
-    "ct_cone_500k": {"sources_sha256_prefix": "1b4cd611142148f0",
-                     "traffic_bytes": 5.0602e8 * 1024 * 2.0 + 2.0179e8 * 1024 * 1.0,
+    "ct_cone_500k": {"sources_sha256_prefix": "7f253653f2ef0e21",
+                     "traffic_bytes": 5.0613e8 * 1024 * 2.0 + 2.0179e8 * 1024 * 1.0,
                      "fused": {"flops": 64 * (6.9993e10 + 1.0210e11 + 6.2141e9), "valu_insts": 1.6803e11},
                      "forward": {"flops": 64 * (2.3526e10 + 7.1946e10 + 4.6594e9), "valu_insts": 8.3451e10}},
     # profiles/fused_fwd_bwd_ct_cone_50k.md
-    "ct_cone_50k": {"sources_sha256_prefix": "1b4cd611142148f0",
-                    "traffic_bytes": 2.3305e6 * 1024 * 2.0 + 2.2556e6 * 1024 * 1.0,
+    "ct_cone_50k": {"sources_sha256_prefix": "7f253653f2ef0e21",
+                    "traffic_bytes": 2.3319e6 * 1024 * 2.0 + 2.2558e6 * 1024 * 1.0,
                     "fused": {"flops": 64 * (6.3639e8 + 9.3517e8 + 5.8120e7), "valu_insts": 1.5752e9},
                     "forward": {"flops": 64 * (2.4787e8 + 6.8108e8 + 4.5218e7), "valu_insts": 8.4237e8}},
     # profiles/fused_fwd_bwd_pet_200k.md
-    "pet_200k": {"sources_sha256_prefix": "1b4cd611142148f0",
-                 "traffic_bytes": 2.0045e8 * 1024 * 2.0 + 1.1438e8 * 1024 * 1.0,
+    "pet_200k": {"sources_sha256_prefix": "7f253653f2ef0e21",
+                 "traffic_bytes": 2.0049e8 * 1024 * 2.0 + 1.1438e8 * 1024 * 1.0,
                  "fused": {"flops": 64 * (3.3671e10 + 5.2734e10 + 3.2284e9), "valu_insts": 8.5079e10},
                  "forward": {"flops": 64 * (1.4048e10 + 3.9726e10 + 2.6154e9), "valu_insts": 4.7385e10}},
 }
